@@ -54,8 +54,12 @@ typedef enum { PSN_F64 = 0, PSN_F32 = 1, PSN_SPLIT = 2 } psn_dtype;
  *                           finite Fourier series of the density on its
  *                           n-point grid (period n h per axis), one forward
  *                           and one backward FFT of size N = n^3 (section 3),
- *                           added after the padded convolution with the
- *                           G-tensor alone.
+ *                           added to the padded convolution with the
+ *                           G-tensor.  The length-n transform of a density is
+ *                           the even outputs of its zero-padded length-2n one,
+ *                           so this too is a term of the padded spectrum (8
+ *                           times the symbol where k0, k1 and k2 are even, 0
+ *                           elsewhere): no extra work per solve either.
  * For a resolved density the two agree far below the method's error (about
  * 1e-13 of max |u| for a Gaussian of width 1 on a 32^3 grid). */
 typedef enum { PSN_CORRECTION_FOLDED = 0, PSN_CORRECTION_FOURIER = 1 } psn_correction;
@@ -206,9 +210,7 @@ psn_status psn_solve_timed(psn_plan *p, const void *rho, void *u, void *stream, 
 psn_status psn_plan_set_schedule(psn_plan *p, int p24, int p3);
 
 /* Choose how the near-zone correction enters (psn_correction); call before
- * psn_kernel_build, since the kernel spectrum differs.  With
- * PSN_CORRECTION_FOURIER a solve also runs the size-N transform pair; its
- * workspace is the plan's (or the batch entry's) own.
+ * psn_kernel_build, since the kernel spectrum differs.
  * Errors: PSN_EINVAL (bad mode, or PSN_CORRECTION_FOURIER on a plan from
  * psn_plan_create_grid with unequal sizes), PSN_ESTATE (already built). */
 psn_status psn_plan_set_correction(psn_plan *p, int mode);
@@ -230,7 +232,8 @@ psn_status psn_plan_gs_table(const psn_plan *p, double *tau, double *w, int cap,
 /* Copy the built kernel spectrum to a host array octant[(n0+1)(n1+1)(n2+1)]
  * ((n+1)^3 on a grid of n points per axis), FP64, index [k0][k1][k2] with
  * k_q = 0..n_q the folded frequency index, in the paper's normalisation (no
- * 1/(8 n0 n1 n2) factor).  Synchronous.
+ * 1/(8 n0 n1 n2) factor).  With PSN_CORRECTION_FOURIER: the G-tensor alone.
+ * Synchronous.
  * Errors: PSN_EINVAL, PSN_ESTATE, PSN_EDEVICE. */
 psn_status psn_kernel_download(const psn_plan *p, double *octant);
 

@@ -127,8 +127,8 @@ class Plan:
     `box=(a, b)` is given, a and b 3-sequences), Gaussian-sum tolerance tol.
     `n` may be a 3-sequence of per-axis point counts (psn_plan_create_grid).
     `correction` is "folded" (the near-zone correction's symbol added to the
-    kernel spectrum) or "fourier" (added after the convolution, with the
-    Laplacian from the density's size-N Fourier series)."""
+    kernel spectrum) or "fourier" (the term that the
+    density's own size-N Fourier series gives for its Laplacian)."""
 
     def __init__(self, n, L: float = None, tol: float = 1e-12, dtype="f32", box=None,
                  correction="folded"):

@@ -3,7 +3,8 @@
 //
 //   a_j(k)   = 2 int_0^T exp(-tau_j^2 y^2) cos(kappa_k y) dy,  kappa_k = 2 pi k / (2 n h)
 //   C0, C2   = int_{B_delta} (U - U_GS) dy,  int_{B_delta} |y|^2 (U - U_GS) dy
-//   K(k)     = sum_j w_j a_j(k0) a_j(k1) a_j(k2) + C0 - (C2/6) |kappa|^2
+//   K(k)     = sum_j w_j a_j(k0) a_j(k1) a_j(k2) + c(k) (C0 - (C2/6) |kappa|^2)
+// with c = correction_weight: 1, or 8 on the all-even frequencies alone.
 //
 // Mode integrals, by the size of tau T:
 // * tau T >= 6.1: the Gaussian's Fourier transform (the tail beyond T is
@@ -205,7 +206,7 @@ __global__ void k_correction(const double* __restrict__ tau, const double* __res
 // octant stores folded with k2 = 0.  Kn[k1 (n + 1) + k0].
 __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__ A1, const double* __restrict__ A2,
                        const double* __restrict__ w, int terms, int n, double p0, double p1, double p2,
-                       const double* __restrict__ Cc, double fold, double* __restrict__ Kn) {
+                       const double* __restrict__ Cc, bool fourier, double* __restrict__ Kn) {
     const int k0 = blockIdx.x * blockDim.x + threadIdx.x, k1 = blockIdx.y;
     if (k0 > n) return;
     const int np1 = n + 1;
@@ -213,7 +214,8 @@ __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__
     for (int j = 0; j < terms; ++j)
         s = fma(A0[size_t(j) * np1 + k0] * A1[size_t(j) * np1 + k1], w[j] * A2[size_t(j) * np1 + n], s);
     const double b0 = 2.0 * kPi * k0 / p0, b1 = 2.0 * kPi * k1 / p1, b2 = 2.0 * kPi * n / p2;
-    Kn[size_t(k1) * np1 + k0] = s + fold * (Cc[0] - (Cc[1] / 6.0) * (b0 * b0 + b1 * b1 + b2 * b2));
+    Kn[size_t(k1) * np1 + k0] =
+        s + psn_host::correction_weight(fourier, k0, k1, n) * (Cc[0] - (Cc[1] / 6.0) * (b0 * b0 + b1 * b1 + b2 * b2));
 }
 
 // Octant assembly, k2 = 0..n-1: a workgroup of 256 threads computes a tile of
@@ -229,7 +231,7 @@ template <class Kt, bool SYM>
 __global__ void __launch_bounds__(256) k_gemm(const double* __restrict__ A0, const double* __restrict__ A1,
                                               const double* __restrict__ A2, const double* __restrict__ w, int terms,
                                               int n, double p0, double p1, double p2,
-                                              const double* __restrict__ Cc, double fold,
+                                              const double* __restrict__ Cc, bool fourier,
                                               const double* __restrict__ Kn, double scale, Kt* __restrict__ K,
                                               Kt* __restrict__ Kb) {
     __shared__ double sa[kChunk][kTile0], sb[kChunk][kTile2], s1[kChunk];
@@ -291,7 +293,8 @@ __global__ void __launch_bounds__(256) k_gemm(const double* __restrict__ A0, con
             const int k2 = k2b + 16 * c + li;
             if (k2 >= n) continue;
             const double b2 = 2.0 * kPi * k2 / p2;
-            const double v = acc[i][c][e] + fold * (C0 - (C2 / 6.0) * (q01 + b2 * b2));
+            const double v = acc[i][c][e] + psn_host::correction_weight(fourier, k0, k1, k2) *
+                                                (C0 - (C2 / 6.0) * (q01 + b2 * b2));
             if (k2 == 0) {
                 const double e = Kn[size_t(k1) * np1 + k0];
                 K[psn_host::k_index(n, k1, k0, 0)] = Kt(scale * 0.5 * (v + e));
@@ -314,8 +317,8 @@ __global__ void __launch_bounds__(256) k_gemm(const double* __restrict__ A0, con
 template <class Kt>
 __global__ void g_assemble(const double* __restrict__ A0, const double* __restrict__ A1,
                            const double* __restrict__ A2, const double* __restrict__ w, int terms, int n0, int n1,
-                           int n2, double p0, double p1, double p2, const double* __restrict__ Cc, double fold,
-                           double scale, Kt* __restrict__ K) {
+                           int n2, double p0, double p1, double p2, const double* __restrict__ Cc, double scale,
+                           Kt* __restrict__ K) {
     const int k2 = blockIdx.x * blockDim.x + threadIdx.x, k1 = blockIdx.y, k0 = blockIdx.z;
     if (k2 >= psn_host::g_pitch(n2)) return;
     if (k2 > n2) {
@@ -327,7 +330,7 @@ __global__ void g_assemble(const double* __restrict__ A0, const double* __restri
         s = fma(A0[size_t(j) * (n0 + 1) + k0] * A1[size_t(j) * (n1 + 1) + k1], w[j] * A2[size_t(j) * (n2 + 1) + k2],
                 s);
     const double b0 = 2.0 * kPi * k0 / p0, b1 = 2.0 * kPi * k1 / p1, b2 = 2.0 * kPi * k2 / p2;
-    const double v = s + fold * (Cc[0] - (Cc[1] / 6.0) * (b0 * b0 + b1 * b1 + b2 * b2));
+    const double v = s + (Cc[0] - (Cc[1] / 6.0) * (b0 * b0 + b1 * b1 + b2 * b2));
     K[psn_host::g_k_index(n0, n2, k0, k1, k2)] = Kt(scale * v);
 }
 
@@ -386,24 +389,22 @@ hipError_t launch_kernel_build(psn_plan* p, const double* d_tau, const double* d
         const dim3 g(unsigned((psn_host::g_pitch(n2) + 127) / 128), n1 + 1, n0 + 1);
         if (p->dtype == PSN_F32)
             hipLaunchKernelGGL(psn::g_assemble<float>, g, dim3(128), 0, s, A[0], A[1], A[2], d_w, terms, n0, n1, n2,
-                               p->period[0], p->period[1], p->period[2], d_c, 1.0, scale, static_cast<float*>(p->K));
+                               p->period[0], p->period[1], p->period[2], d_c, scale, static_cast<float*>(p->K));
         else
             hipLaunchKernelGGL(psn::g_assemble<double>, g, dim3(128), 0, s, A[0], A[1], A[2], d_w, terms, n0, n1, n2,
-                               p->period[0], p->period[1], p->period[2], d_c, 1.0, scale, static_cast<double*>(p->K));
+                               p->period[0], p->period[1], p->period[2], d_c, scale, static_cast<double*>(p->K));
         return hipGetLastError();
     }
-    // the correction symbol is folded into K unless the plan adds it by the
-    // Fourier series of the density (then fold = 0 leaves the G-tensor alone)
-    const double fold = p->correction == PSN_CORRECTION_FOURIER ? 0.0 : 1.0;
+    const bool fourier = p->correction == PSN_CORRECTION_FOURIER;
     hipLaunchKernelGGL(psn::k_edge, dim3((n + 1 + 127) / 128, n + 1), dim3(128), 0, s, A[0], A[1], A[2], d_w, terms,
-                       n, p->period[0], p->period[1], p->period[2], d_c, fold, d_kn);
+                       n, p->period[0], p->period[1], p->period[2], d_c, fourier, d_kn);
     const double M = 2.0 * n;
     const double scale = 1.0 / (M * M * M);
     const bool sym = A[0] == A[1];
     const dim3 grid((n + psn::kTile2 - 1) / psn::kTile2, (n + 1 + psn::kTile0 - 1) / psn::kTile0, n + 1);
 #define PSN_GEMM(KT, SYMV)                                                                                         \
     hipLaunchKernelGGL((psn::k_gemm<KT, SYMV>), grid, dim3(256), 0, s, A[0], A[1], A[2], d_w, terms, n,            \
-                       p->period[0], p->period[1], p->period[2], d_c, fold, d_kn, scale, static_cast<KT*>(p->K),   \
+                       p->period[0], p->period[1], p->period[2], d_c, fourier, d_kn, scale, static_cast<KT*>(p->K),   \
                        static_cast<KT*>(p->Kb))
     if (p->dtype == PSN_F32) {
         if (sym) PSN_GEMM(float, true);

@@ -1022,217 +1022,11 @@ p5_c2r(const Batch<DT> bt) {
     }
 }
 
-// ------------------------------------------------------------------ Fourier-series correction
-// The near-zone correction by the paper's own route (section 2: derivatives
-// from the finite Fourier series of the density, one forward and one
-// backward FFT of size N = n^3, section 3): z = C0 rho + (C2/6) Laplace_N(rho),
-// with the Laplacian's symbol -sum_q kappa_q^2, kappa_q = 2 pi k / (n h_q) at
-// the signed index k (period n h_q, the samples' own grid).  It runs after
-// the axis-1 inverse, while rho is intact (also in place) and W2 is free: z
-// lives in W2's memory, as n^3 complex values in C order.  Five line passes,
-// each one read and one write of the volume: axis 2 forward reading rho
-// itself; axis 1 forward; axis 0 forward, times the symbol
-// (C0 - (C2/6) |kappa|^2) / n^3, inverse (one pass, radices reversed as in
-// the middle pass of the solve); axis 1 inverse; and, after the solve's
-// axis-2 pass, axis 2 inverse adding Re z to u.
-template <int DT>
-struct CorrProb {
-    const typename Prec<DT>::Io* rho;
-    typename Prec<DT>::Io* u;
-    cx<typename Prec<DT>::Real>* z;
-    const cx<typename Prec<DT>::Real>* tw;
-    double c0, c2;   // C0 and C2 / 6
-    double kq[3];    // 2 pi / (n h_q)
-};
-template <int DT>
-struct CorrBatch {
-    int count;
-    CorrProb<DT> p[kMaxBatch];
-};
-
-// Length-N transforms of the real density along each axis (DIR = -1
-// forward, +1 inverse, unnormalised), on its half spectrum z[i0][i1][k2],
-// k2 = 0..N/2, rows padded to HZ.  Axis 2: a workgroup holds LC contiguous
-// lines, one LDS row each; the forward reads a row of rho as N/2 complex
-// pairs, transforms them at length N/2 and unpacks the N/2 + 1 outputs (as
-// P1), the inverse packs them back and adds the row to u (as P5).  Axes 0
-// and 1: a workgroup holds B adjacent lines (consecutive k2), element-major
-// in LDS, so each point's B values are one contiguous run; on axis 0 the
-// forward is followed in registers by the symbol and the inverse (DIR is
-// ignored there).
-template <int N, int DT>
-struct CorrCfg {
-    using Real = typename Prec<DT>::Real;
-    static constexpr int CX = sizeof(cx<Real>);
-    // axis 2: packed transforms of length N/2
-    static constexpr int E = elems_per_thread(N / 2, sizeof(Real));
-    static constexpr int T = N / 2 / E;
-    static constexpr int LC = pick_lines(N / 2, T, CX, 256, kMaxLds);  // axis-2 lines
-    static constexpr int NP = rows_padded(N / 2);
-    // axes 0 and 1: at most 8 elements per thread (FP32 otherwise takes 16),
-    // so that the three workgroups that fit a CU's LDS hold twice the waves
-    static constexpr int T01 = N / elems_per_thread(N, 8);
-    static constexpr int B = (N % 8 == 0 && (8 * N + TwLds<Real>::slots(N)) * CX <= 65536 && 8 * T01 <= 1024) ? 8
-                             : (N % 4 == 0 && (4 * N + TwLds<Real>::slots(N)) * CX <= 65536) ? 4
-                                                                                              : 1;
-    static constexpr int HZ = (N / 2 + B) / B * B;  // N/2 + 1 rounded up to B
-};
-
-template <int N, int DT, int AX, int DIR>
-__global__ void corr_fft(const CorrBatch<DT> cb) {
-    using CC = CorrCfg<N, DT>;
-    using Real = typename CC::Real;
-    extern __shared__ __align__(16) unsigned char smem[];
-    cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
-    const CorrProb<DT>& P = cb.p[blockIdx.y];
-    cx<Real>* __restrict__ z = P.z;
-    if constexpr (AX == 2) {
-        // packed length FL = N/2: z_j = x_2j + i x_2j+1, Z = DFT_FL(z),
-        // X[k] = (Z[k] + conj Z[FL-k])/2 + w^k (Z[k] - conj Z[FL-k])/(2i),
-        // w = exp(-2 pi i / N), X[0] and X[FL] from Z[0]; the inverse packs
-        // Y[k] = (X[k] + conj X[FL-k]) + i w^-k (X[k] - conj X[FL-k]) and
-        // IDFT_FL(Y)_j = u_2j + i u_2j+1
-        constexpr int FL = N / 2;
-        using F = TeamFFT<FL, CC::T, Real, DIR, false>;
-        cx<Real> d[F::E];
-        using Io = typename Prec<DT>::Io;
-        const int t = threadIdx.x % CC::T, ln = threadIdx.x / CC::T;
-        const size_t line = size_t(blockIdx.x) * CC::LC + ln;
-        const size_t base = line * N;  // of rho and u
-        cx<Real>* const zr = z + line * CC::HZ;
-        // the length-FL table exp(-2 pi i m / N), m < N: every other entry of
-        // the plan's length-2N table
-        TwLds<Real> tl{sb + CC::LC * CC::NP};
-        for (int i = threadIdx.x; i < N; i += CC::LC * CC::T) tl.p[TwLds<Real>::at(i)] = P.tw[2 * i];
-        __syncthreads();
-        LdsRows<Real> lds{sb + ln * CC::NP};
-        if constexpr (DIR < 0) {
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) {
-                const int j = F::in_pos(t, e);
-                d[e] = {Real(P.rho[base + 2 * j]), Real(P.rho[base + 2 * j + 1])};
-            }
-            F::run1(d, t, tl, lds);
-            __syncthreads();  // the transform's last exchange reads are done
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) lds.put(F::out_pos(t, e), d[e]);
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) {
-                const int k = F::out_pos(t, e);
-                const cx<Real> Z = lds.get(k);
-                if (k == 0) {
-                    gst(zr, cx<Real>{Z.x + Z.y, Real(0)});
-                    gst(zr + FL, cx<Real>{Z.x - Z.y, Real(0)});
-                } else {
-                    const cx<Real> Zr = conj(lds.get(FL - k));
-                    const cx<Real> Ev = scale(Z + Zr, Real(0.5));
-                    const cx<Real> Od = rot<-1>(scale(Z - Zr, Real(0.5)));
-                    gst(zr + k, Ev + Od * tl(k));
-                }
-            }
-        } else {
-            // each X[k] loaded once into the line's row (X[FL] by its first
-            // thread); the partner X[FL-k] read back from there
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) d[e] = gld(zr + F::in_pos(t, e));
-            const cx<Real> last = t == 0 ? gld(zr + FL) : cx<Real>{Real(0), Real(0)};
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) lds.put(F::in_pos(t, e), d[e]);
-            if (t == 0) lds.put(FL, last);
-            __syncthreads();
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) {
-                const int k = F::in_pos(t, e);
-                const cx<Real> p = d[e], q = conj(lds.get(FL - k));
-                d[e] = (p + q) + rot<+1>(mul_conj(p - q, tl(k)));
-            }
-            F::run1(d, t, tl, lds);  // its first exchange waits before reusing the row
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) {
-                const int j = F::out_pos(t, e);
-                Io* __restrict__ u = P.u + base + 2 * j;
-                u[0] = Io(u[0] + Io(d[e].x));
-                u[1] = Io(u[1] + Io(d[e].y));
-            }
-        }
-    } else {
-        constexpr int B = CC::B, TT = CC::T01;
-        using F = TeamFFT<N, TT, Real, DIR, false>;
-        cx<Real> d[F::E];
-        // units (line, tile of B columns k2), tiles fastest, dealt XCD-aware
-        // so that neighbouring tiles (which share 128-byte lines) meet in one
-        // L2; columns past k2 = N/2 transform the row padding
-        constexpr int HZ = CC::HZ;
-        constexpr int units = N * (HZ / B);
-        const int u = xcd_unit();
-        if (u >= units) return;  // whole workgroup
-        const int c = threadIdx.x % B, t = threadIdx.x / B;
-        const int line = u / (HZ / B), i2 = (u % (HZ / B)) * B + c;
-        // axis 1: (i0 = line, pos, k2 = i2); axis 0: (pos, i1 = line, k2 = i2)
-        const size_t stride = AX == 1 ? size_t(HZ) : size_t(N) * HZ;
-        const size_t base = (AX == 1 ? size_t(line) * N * HZ : size_t(line) * HZ) + i2;
-        TwLds<Real> tl{sb + B * N};
-        tl.fill(P.tw, N, threadIdx.x, B * TT);
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < F::E; ++e) d[e] = gld(z + base + size_t(F::in_pos(t, e)) * stride);
-        LdsCols<Real> lds{sb, B, c};
-        F::run1(d, t, tl, lds);
-        if constexpr (AX == 0) {
-            // z *= (C0 - (C2/6) |kappa|^2) / n^3 at (k0, k1 = line, k2 = i2), then the
-            // inverse with the radices reversed, which starts from this layout
-            using Fi = TeamFFT<N, TT, Real, +1, true>;
-            auto kap2 = [](double kq, int k) {
-                const double v = kq * double(k <= N / 2 ? k : k - N);
-                return v * v;
-            };
-            const double q12 = kap2(P.kq[1], line) + kap2(P.kq[2], i2);
-            const double inv = 1.0 / (double(N) * N * N);
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) {
-                const double q = q12 + kap2(P.kq[0], F::out_pos(t, e));
-                d[e] = scale(d[e], Real((P.c0 - P.c2 * q) * inv));
-            }
-            __syncthreads();  // the forward's last exchange reads are done
-            Fi::run1(d, t, tl, lds);
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) gst(z + base + size_t(Fi::out_pos(t, e)) * stride, d[e]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < F::E; ++e) gst(z + base + size_t(F::out_pos(t, e)) * stride, d[e]);
-        }
-    }
-}
-
 // ------------------------------------------------------------------ launcher
 // Kernels needing more than 64 KB of dynamic LDS must say so once.
 inline bool allow_lds(const void* fn, size_t bytes) {
     if (bytes <= 65536) return true;
     return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) == hipSuccess;
-}
-
-// The correction's passes before the solve's axis-2 pass (z after the
-// axis-1 inverse) and the one after it (axis-2 inverse added to u).
-template <int N, int DT>
-hipError_t launch_corr_z(const CorrBatch<DT>& cb, hipStream_t s) {
-    using CC = CorrCfg<N, DT>;
-    const size_t lds2 = (size_t(CC::LC) * CC::NP + TwLds<typename CC::Real>::slots(N / 2)) * CC::CX;
-    const size_t lds01 = (size_t(CC::B) * N + TwLds<typename CC::Real>::slots(N)) * CC::CX;
-    const dim3 g2(N * N / CC::LC, cb.count), g01(xcd_grid(N * (CC::HZ / CC::B)), cb.count);
-    const dim3 b2(CC::LC * CC::T), b01(CC::B * CC::T01);
-    hipLaunchKernelGGL((corr_fft<N, DT, 2, -1>), g2, b2, lds2, s, cb);
-    hipLaunchKernelGGL((corr_fft<N, DT, 1, -1>), g01, b01, lds01, s, cb);
-    hipLaunchKernelGGL((corr_fft<N, DT, 0, -1>), g01, b01, lds01, s, cb);
-    hipLaunchKernelGGL((corr_fft<N, DT, 1, +1>), g01, b01, lds01, s, cb);
-    return hipGetLastError();
-}
-template <int N, int DT>
-hipError_t launch_corr_add(const CorrBatch<DT>& cb, hipStream_t s) {
-    using CC = CorrCfg<N, DT>;
-    const size_t lds2 = (size_t(CC::LC) * CC::NP + TwLds<typename CC::Real>::slots(N / 2)) * CC::CX;
-    hipLaunchKernelGGL((corr_fft<N, DT, 2, +1>), dim3(N * N / CC::LC, cb.count), dim3(CC::LC * CC::T), lds2, s, cb);
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ schedules
@@ -1459,12 +1253,8 @@ hipError_t launch_p3v(const Batch<DT>& bt, hipStream_t s, int v) {
 
 // Enqueue the six kernels of one solve for bt.count problems of size N with
 // schedule (v24 for P2/P4, v3 for P3).
-// With cb (the entries whose plan adds the correction by its Fourier series),
-// z is formed after the axis-1 inverse and added after the axis-2 pass
-// (both counted in the last pass's event interval).
 template <int N, int DT>
-hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, int v3,
-                   const CorrBatch<DT>* cb = nullptr) {
+hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, int v3) {
     using C = Cfg<N, DT>;
     constexpr size_t tws = TwLds<typename C::Real>::slots(N);
     const size_t lds_rows = (size_t(C::LC) * C::NP + tws) * C::CX;
@@ -1487,9 +1277,7 @@ hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, 
     mark(3);
     if ((e = launch_p24<N, DT>(bt, s, v24, false)) != hipSuccess) return e;
     mark(4);
-    if (cb && (e = launch_corr_z<N, DT>(*cb, s)) != hipSuccess) return e;
     hipLaunchKernelGGL((p5_c2r<N, DT>), dim3(xcd_grid(cnt * N * N / C::LC)), dim3(C::LC * C::T), lds_rows, s, bt);
-    if (cb && (e = launch_corr_add<N, DT>(*cb, s)) != hipSuccess) return e;
     mark(5);
     return hipGetLastError();
 }
@@ -1562,22 +1350,6 @@ Prob<DT> prob_of(const psn_host::Slot& sl) {
     return pr;
 }
 
-template <int DT>
-CorrProb<DT> corr_of(const psn_host::Slot& sl) {
-    using Real = typename Prec<DT>::Real;
-    using Io = typename Prec<DT>::Io;
-    const psn_plan* p = sl.plan;
-    CorrProb<DT> c{};
-    c.rho = static_cast<const Io*>(sl.rho);
-    c.u = static_cast<Io*>(sl.u);
-    c.z = static_cast<cx<Real>*>(sl.W2);  // free between the axis-1 inverse and the end of the solve
-    c.tw = static_cast<const cx<Real>*>(p->tw);
-    c.c0 = p->C0;
-    c.c2 = p->C2 / 6.0;
-    for (int q = 0; q < 3; ++q) c.kq[q] = 2.0 * 3.14159265358979323846 / (double(p->n) * p->h[q]);
-    return c;
-}
-
 // Slots [0, count) share n, precision and schedule (the caller groups them
 // so); v24/v3 >= 0 override the plans' schedule.
 template <int DT>
@@ -1586,18 +1358,12 @@ hipError_t solve_group(const psn_host::Slot* slots, int count, hipStream_t s, hi
     const int v24 = v24o >= 0 ? v24o : slots[0].plan->sched24, v3 = v3o >= 0 ? v3o : slots[0].plan->sched3;
     for (int base = 0; base < count; base += kMaxBatch) {
         Batch<DT> bt{};
-        CorrBatch<DT> cb{};
         bt.count = count - base < kMaxBatch ? count - base : kMaxBatch;
-        for (int i = 0; i < bt.count; ++i) {
-            const psn_host::Slot& sl = slots[base + i];
-            bt.p[i] = prob_of<DT>(sl);
-            if (sl.plan->correction == PSN_CORRECTION_FOURIER) cb.p[cb.count++] = corr_of<DT>(sl);
-        }
-        const CorrBatch<DT>* cbp = cb.count > 0 ? &cb : nullptr;
+        for (int i = 0; i < bt.count; ++i) bt.p[i] = prob_of<DT>(slots[base + i]);
         hipError_t e = hipErrorInvalidValue;
         switch (slots[0].plan->n) {
 #define PSN_CASE(NN) \
-    case NN: e = solve_n<NN, DT>(bt, s, ev, v24, v3, cbp); break;
+    case NN: e = solve_n<NN, DT>(bt, s, ev, v24, v3); break;
             PSN_FOR_EACH_SIZE(PSN_CASE)
 #undef PSN_CASE
             default: break;

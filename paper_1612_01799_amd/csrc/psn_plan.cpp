@@ -919,6 +919,13 @@ psn_status psn_kernel_download(const psn_plan* p, double* octant) {
         return reinterpret_cast<const double*>(v.data())[i];
     };
     const double M = 2.0 * n, inv = M * M * M;
+    // with the correction by the Fourier series the octant is the G-tensor
+    // alone: the symbol that K also holds is taken off again
+    const bool fourier = p->correction == PSN_CORRECTION_FOURIER;
+    auto kap2 = [&](int q, size_t k) {
+        const double v = 2.0 * kPi * double(k) / p->period[q];
+        return v * v;
+    };
     for (size_t a = 0; a < np1; ++a)
         for (size_t b = 0; b < np1; ++b) {
             double* dst = octant + (a * np1 + b) * np1;
@@ -926,6 +933,10 @@ psn_status psn_kernel_download(const psn_plan* p, double* octant) {
             dst[0] = (al + be) * inv;
             dst[n] = (al - be) * inv;
             for (size_t c = 1; c < n; ++c) dst[c] = get(hk, psn_host::k_index(int(n), int(b), int(a), int(c))) * inv;
+            if (!fourier) continue;
+            for (size_t c = 0; c <= n; ++c)
+                dst[c] -= psn_host::correction_weight(true, int(a), int(b), int(c)) *
+                          (p->C0 - (p->C2 / 6.0) * (kap2(0, a) + kap2(1, b) + kap2(2, c)));
         }
     return PSN_OK;
 }
