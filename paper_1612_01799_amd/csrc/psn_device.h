@@ -162,6 +162,35 @@ struct DFT<12, DIR, T> : PrimeFactorDFT<4, 3, DIR, T> {};
 template <int DIR, class T>
 struct DFT<20, DIR, T> : PrimeFactorDFT<4, 5, DIR, T> {};
 
+// Radix 9 as two layers of radix-3 butterflies.
+template <int DIR, class T>
+struct DFT<9, DIR, T> {
+    static __device__ __forceinline__ void run(cx<T>* v) {
+        // exp(2 pi i e / 9) for the exponents j0 k1 = 1, 2, 4 between the layers
+        const T c[5] = {T(1), T(0.76604444311897803520), T(0.17364817766693034885), T(-0.5), T(-0.93969262078590838405)};
+        const T s[5] = {T(0), T(0.64278760968653932632), T(0.98480775301220805937), T(0.86602540378443864676),
+                        T(0.34202014332566873304)};
+        cx<T> a[3][3];
+#pragma unroll
+        for (int j0 = 0; j0 < 3; ++j0) {
+#pragma unroll
+            for (int j1 = 0; j1 < 3; ++j1) a[j0][j1] = v[j0 + 3 * j1];
+            DFT<3, DIR, T>::run(a[j0]);
+        }
+#pragma unroll
+        for (int k1 = 0; k1 < 3; ++k1) {
+            cx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+            if (k1 > 0) {
+                b[1] = b[1] * cx<T>{c[k1], T(DIR) * s[k1]};
+                b[2] = b[2] * cx<T>{c[2 * k1], T(DIR) * s[2 * k1]};
+            }
+            DFT<3, DIR, T>::run(b);
+#pragma unroll
+            for (int k0 = 0; k0 < 3; ++k0) v[k1 + 3 * k0] = b[k0];
+        }
+    }
+};
+
 // Radix 8 as three layers of radix-2 butterflies.  The first layer pairs
 // inputs j and j+4 (s = v_j + v_j+4, d = v_j - v_j+4); its variants below fold
 // an input twiddle or an input scale into the butterfly with fused
@@ -265,12 +294,13 @@ struct RadixPlan {
 };
 
 // Stages for a length-N transform with E elements per thread: odd radices
-// first, each merged with a factor 4 or 2 into one prime-factor radix (20, 12,
+// first (9 for two factors 3), each merged with a factor 4 or 2 into one prime-factor radix (20, 12,
 // 10, 6) where that divides both what is left of N and E; then the largest
 // power-of-two radix (<= 16) dividing both what is left of N and the
 // power-of-two part of E, so each stage gives every thread a whole number of
 // butterflies.
 constexpr int odd_radix(int f, int rem, int E) {
+    if (f == 3 && rem % 9 == 0 && E % 9 == 0) return 9;
     for (int p = 4; p >= 1; p /= 2)
         if (rem % (f * p) == 0 && E % (f * p) == 0) return f * p;
     return -1;
@@ -299,26 +329,51 @@ constexpr RadixPlan make_plan(int N, int E) {
     return p;
 }
 
-// Elements per thread for a length-N line: N's odd factors, at most 15 of
-// them (an odd part above 15, such as 81, keeps its largest divisor up to 9:
-// radix-3 stages then fill the rest), times up to 16 (N a power of two; 8
-// for 8-byte reals) or 4 (N with a factor 3 or 5) of its powers of two.
+// Lines of 48 points and more with an odd factor: three stages 8, m, g (9, 2, 9
+// for 162; 9, 9 for 81) with m the odd factor (6 for 384).  A thread then holds at most 8 to
+// 12 elements instead of the 12 to 20 that keeping the odd factor in every stage
+// takes; the N / R butterflies of a stage are dealt to the team in rounds, and
+// a partly filled round leaves threads idle (TeamFFT::has).
+constexpr bool mid_plan(int N) { return N >= 48 && (N & (N - 1)) != 0; }
+// A team that holds 12 or 20 elements per thread still takes the stages that
+// keep the odd factor in every thread (384 = 12.4.4.2 on 32 threads).
+constexpr int odd_part(int N) { return N % 2 ? N : odd_part(N / 2); }
+constexpr RadixPlan team_plan(int N, int E) {
+    if (!mid_plan(N) || (odd_part(N) <= 5 && E % (4 * odd_part(N)) == 0)) return make_plan(N, E);
+    const int first = N % 8 == 0 ? 8 : 9, rem = N / first;
+    int last = first;
+    while (rem % last != 0) last = first == 8 ? last / 2 : last / 3;
+    const int mid = rem / last;
+    if (mid == 1) return RadixPlan{2, {first, last}};
+    return mid == 2 || mid == 3 || mid == 5 || mid == 6 ? RadixPlan{3, {first, mid, last}} : RadixPlan{-1, {}};
+}
+
+// Elements per thread for a length-N line of the contiguous passes: a power of
+// two takes up to 16 (8 for 8-byte reals), a line with an odd factor 8 (or 9)
+// from 48 points on, where its outer stages then fill every lane; shorter ones
+// keep their odd factors in every thread, times up to 4 of the powers of two.
 constexpr int elems_per_thread(int N, int real_bytes) {
     int odd = N;
     while (odd % 2 == 0) odd /= 2;
-    int p2 = N / odd;
-    int cap = odd == 1 ? (real_bytes == 8 ? 8 : 16) : 4;
-    int oe = odd;
-    if (oe > 15) {
-        oe = 1;
-        for (int d = 9; d >= 1; --d)
-            if (odd % d == 0) {
-                oe = d;
-                break;
-            }
-        cap = 2;
-    }
-    return oe * (p2 < cap ? p2 : cap);
+    const int p2 = N / odd;
+    if (odd == 1) return p2 < (real_bytes == 8 ? 8 : 16) ? p2 : (real_bytes == 8 ? 8 : 16);
+    // (FP32 lines of 96 and 160 points: 13 densities' P1 27 and 111 us with 12
+    // and 20 elements, 31 and 124 us with 8)
+    if (mid_plan(N) && !(real_bytes == 4 && N < 192 && odd <= 5)) return N % 8 == 0 ? 8 : 9;
+    return odd * (p2 < 4 ? p2 : 4);
+}
+// Threads per line of the strided passes: at most 8 elements each; with an odd
+// factor the next power of two, so that 4 or 8 lines make workgroups of 4 or 8
+// whole waves.  (Measured at n = 384 FP64: with 48 threads per line, 6 waves per
+// workgroup, only one workgroup was resident per CU where registers and LDS
+// allow two, and the axis-1 forward pass took 0.86 ms.)  The idle threads of
+// the outer stages are whole waves and cost no issue slots.
+constexpr int strided_team(int N) {
+    const int t = N / elems_per_thread(N, 8);
+    if (!mid_plan(N) || N % 8 != 0) return t;
+    int p = 1;
+    while (p < t) p *= 2;
+    return p;
 }
 
 // ----------------------------------------------------------------- twiddle sources
@@ -381,24 +436,37 @@ struct Single {
 // slot e holds input position in_pos(t, e); on exit it holds output position
 // out_pos(t, e).  Between stages the team exchanges through an LDS view
 // (`Lds::put/get` at a position, `Lds::sync` = workgroup barrier).
+// E, EI, EO, EM: elements per thread on average, slots of the first stage, of the
+// last one and of the largest.  They differ only with mid_plan(N), where a
+// stage's N / R butterflies need not fill its rounds: slots of a round without
+// a butterfly are skipped (each_in, each_out for a caller's loads and stores).
 // With REV the radices run in reverse order; a REV transform's in_pos is the
 // forward transform's out_pos, so a forward pass and a REV inverse pass can be
 // chained in registers (used for the fused multiply of the middle pass).
 template <int N, int T, class Real, int DIR, bool REV>
 struct TeamFFT {
     static constexpr int E = N / T;
-    static constexpr RadixPlan plan = make_plan(N, E);
+    static constexpr RadixPlan plan = team_plan(N, E);
     static constexpr int S = plan.n;
     static_assert(N % T == 0, "team must divide the line");
     static_assert(S > 0, "no radix plan for this size");
-    static constexpr bool radices_divide_e() {
-        for (int i = 0; i < S; ++i)
-            if (E % plan.r[i] != 0) return false;
-        return true;
-    }
-    static_assert(radices_divide_e(), "every radix must divide the elements per thread");
-
     static constexpr int radix(int i) { return REV ? plan.r[S - 1 - i] : plan.r[i]; }
+    // rounds of butterflies of stage i, and its slots per thread
+    static constexpr int rounds(int i) { return (N / radix(i) + T - 1) / T; }
+    static constexpr int slots(int i) { return rounds(i) * radix(i); }
+    static constexpr int max_slots() {
+        int m = 0;
+        for (int i = 0; i < S; ++i) m = slots(i) > m ? slots(i) : m;
+        return m;
+    }
+    static constexpr int EI = slots(0), EO = slots(S - 1), EM = max_slots();
+    // whether thread t has a butterfly in round s of stage I (known at compile
+    // time for all but a partly filled last round)
+    template <int I>
+    static __device__ __forceinline__ bool has(int t, int s) {
+        constexpr int NB = N / radix(I);
+        return T * (s + 1) <= NB || t + T * s < NB;
+    }
     static constexpr int span(int i) {
         int ns = 1;
         for (int q = 0; q < i; ++q) ns *= radix(q);
@@ -459,6 +527,42 @@ struct TeamFFT {
     static __device__ __forceinline__ int out_pos(int t, int e) {
         return t + T * (e / RL) + (e % RL) * (N / RL);
     }
+    // f(e) for the slots e in which thread t holds an element on entry (on
+    // exit).  One branch per round, so that the loads of a round are issued
+    // together.
+    template <class Fn>
+    static __device__ __forceinline__ void each_in(int t, Fn&& f) {
+        if constexpr (N / R0 % T == 0) {
+#pragma unroll
+            for (int e = 0; e < EI; ++e) f(e);
+        } else {
+#pragma unroll
+            for (int s = 0; s < EI / R0; ++s) {
+                if (!has<0>(t, s)) continue;
+#pragma unroll
+                for (int r = 0; r < R0; ++r) f(s * R0 + r);
+            }
+        }
+    }
+    template <class Fn>
+    static __device__ __forceinline__ void each_out(int t, Fn&& f) {
+        if constexpr (N / RL % T == 0) {
+#pragma unroll
+            for (int e = 0; e < EO; ++e) f(e);
+        } else {
+#pragma unroll
+            for (int s = 0; s < EO / RL; ++s) {
+                if (!has<S - 1>(t, s)) continue;
+#pragma unroll
+                for (int r = 0; r < RL; ++r) f(s * RL + r);
+            }
+        }
+    }
+    // largest t that holds slot e on exit
+    static constexpr int out_last(int e) {
+        const int left = N / RL - T * (e / RL);
+        return (left < T ? left : T) - 1;
+    }
 
     // NC independent lines per thread advance together: one barrier pair per
     // exchange serves all of them.  `lds` stores the NC values of one position
@@ -466,23 +570,28 @@ struct TeamFFT {
     // constant); `tw(m)` returns exp(-2 pi i m / 2N).
     // ks: if not null, per-element real scales applied to the input of stage 0
     template <int I, int NC, class Lds, class Tw>
-    static __device__ __forceinline__ void stage(cx<Real> (&d)[NC][E], int t, const Tw& tw, Lds& lds,
-                                                 const Real (*ks)[E] = nullptr) {
+    static __device__ __forceinline__ void stage(cx<Real> (&d)[NC][EM], int t, const Tw& tw, Lds& lds,
+                                                 const Real (*ks)[EI] = nullptr) {
         if constexpr (I < S) {
             constexpr int R = radix(I);
             constexpr int Ns = span(I);
             constexpr int twstep = 2 * N / (Ns * R);
             if constexpr (I > 0 && !Lds::kSeq) {
 #pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    cx<Real> v[NC];
-                    lds.get2(t, T * (e / R) + (e % R) * (N / R), v);
+                for (int s = 0; s < rounds(I); ++s) {
+                    if (!has<I>(t, s)) continue;
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) d[c][e] = v[c];
+                    for (int r = 0; r < R; ++r) {
+                        cx<Real> v[NC];
+                        lds.get2(t, T * s + r * (N / R), v);
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) d[c][s * R + r] = v[c];
+                    }
                 }
             }
 #pragma unroll
-            for (int s = 0; s < E / R; ++s) {
+            for (int s = 0; s < rounds(I); ++s) {
+                if (!has<I>(t, s)) continue;
                 cx<Real> w[R];
                 if constexpr (Ns > 1) {
                     if constexpr (Tw::kRows) {
@@ -520,14 +629,14 @@ struct TeamFFT {
                 }
             }
             if constexpr (I + 1 < S) {
-                // output position of slot e as (per-thread base, constant offset)
-                auto put_at = [&](int e, int& base, int& off) {
+                // output position of slot s R + r as (per-thread base, constant offset)
+                auto put_at = [&](int s, int r, int& base, int& off) {
                     if constexpr (T % Ns == 0) {
                         base = (t / Ns) * Ns * R + t % Ns;
-                        off = T * (e / R) * R + (e % R) * Ns;
+                        off = T * s * R + r * Ns;
                     } else {
-                        const int b = t + T * (e / R);
-                        base = (b / Ns) * Ns * R + (b % Ns) + (e % R) * Ns;
+                        const int b = t + T * s;
+                        base = (b / Ns) * Ns * R + (b % Ns) + r * Ns;
                         off = 0;
                     }
                 };
@@ -540,33 +649,45 @@ struct TeamFFT {
                     for (int c0 = 0; c0 < NC; c0 += G) {
                         lds.sync();
 #pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            int base, off;
-                            put_at(e, base, off);
-                            cx<Real> v[G];
+                        for (int s = 0; s < rounds(I); ++s) {
+                            if (!has<I>(t, s)) continue;
 #pragma unroll
-                            for (int g = 0; g < G; ++g) v[g] = d[c0 + g][e];
-                            lds.putg(base, off, v);
+                            for (int r = 0; r < R; ++r) {
+                                int base, off;
+                                put_at(s, r, base, off);
+                                cx<Real> v[G];
+#pragma unroll
+                                for (int g = 0; g < G; ++g) v[g] = d[c0 + g][s * R + r];
+                                lds.putg(base, off, v);
+                            }
                         }
                         lds.sync();
 #pragma unroll
-                        for (int e = 0; e < E; ++e) {
-                            cx<Real> v[G];
-                            lds.getg(t, T * (e / R2) + (e % R2) * (N / R2), v);
+                        for (int s = 0; s < rounds(I + 1); ++s) {
+                            if (!has<I + 1>(t, s)) continue;
 #pragma unroll
-                            for (int g = 0; g < G; ++g) d[c0 + g][e] = v[g];
+                            for (int r = 0; r < R2; ++r) {
+                                cx<Real> v[G];
+                                lds.getg(t, T * s + r * (N / R2), v);
+#pragma unroll
+                                for (int g = 0; g < G; ++g) d[c0 + g][s * R2 + r] = v[g];
+                            }
                         }
                     }
                 } else {
                     lds.sync();
 #pragma unroll
-                    for (int e = 0; e < E; ++e) {
-                        cx<Real> v[NC];
+                    for (int s = 0; s < rounds(I); ++s) {
+                        if (!has<I>(t, s)) continue;
 #pragma unroll
-                        for (int c = 0; c < NC; ++c) v[c] = d[c][e];
-                        int base, off;
-                        put_at(e, base, off);
-                        lds.put2(base, off, v);
+                        for (int r = 0; r < R; ++r) {
+                            cx<Real> v[NC];
+#pragma unroll
+                            for (int c = 0; c < NC; ++c) v[c] = d[c][s * R + r];
+                            int base, off;
+                            put_at(s, r, base, off);
+                            lds.put2(base, off, v);
+                        }
                     }
                     lds.sync();
                 }
@@ -576,19 +697,19 @@ struct TeamFFT {
     }
 
     template <int NC, class Lds, class Tw>
-    static __device__ __forceinline__ void run(cx<Real> (&d)[NC][E], int t, const Tw& tw, Lds& lds) {
+    static __device__ __forceinline__ void run(cx<Real> (&d)[NC][EM], int t, const Tw& tw, Lds& lds) {
         stage<0, NC>(d, t, tw, lds);
     }
     // the same, with the input of chain c, slot e first multiplied by the real ks[c][e]
     template <int NC, class Lds, class Tw>
-    static __device__ __forceinline__ void run_scaled(cx<Real> (&d)[NC][E], int t, const Tw& tw, Lds& lds,
-                                                      const Real (&ks)[NC][E]) {
+    static __device__ __forceinline__ void run_scaled(cx<Real> (&d)[NC][EM], int t, const Tw& tw, Lds& lds,
+                                                      const Real (&ks)[NC][EI]) {
         stage<0, NC>(d, t, tw, lds, ks);
     }
 
     // single line per thread, twiddles from a global table
     template <class Lds>
-    static __device__ __forceinline__ void run(cx<Real> (&d)[E], int t, const cx<Real>* __restrict__ tw,
+    static __device__ __forceinline__ void run(cx<Real> (&d)[EM], int t, const cx<Real>* __restrict__ tw,
                                                Lds& lds) {
         TwGlobal<Real> g{tw};
         run1(d, t, g, lds);
@@ -596,14 +717,14 @@ struct TeamFFT {
 
     // single line per thread, any twiddle source
     template <class Lds, class Tw>
-    static __device__ __forceinline__ void run1(cx<Real> (&d)[E], int t, const Tw& tw, Lds& lds) {
-        cx<Real> dd[1][E];
+    static __device__ __forceinline__ void run1(cx<Real> (&d)[EM], int t, const Tw& tw, Lds& lds) {
+        cx<Real> dd[1][EM];
 #pragma unroll
-        for (int e = 0; e < E; ++e) dd[0][e] = d[e];
+        for (int e = 0; e < EM; ++e) dd[0][e] = d[e];
         Single<Lds> l1{lds};
         stage<0, 1>(dd, t, tw, l1);
 #pragma unroll
-        for (int e = 0; e < E; ++e) d[e] = dd[0][e];
+        for (int e = 0; e < EM; ++e) d[e] = dd[0][e];
     }
 };
 
@@ -765,6 +886,20 @@ template <class T>
 __device__ __forceinline__ T* sbase(T* p) {
     asm("" : "+s"(p));
     return p;
+}
+// The same, and a fresh value wherever it stands: loads from the returned
+// pointer are neither shared with earlier ones nor moved up past a barrier
+// before it, so their results are live from here on only.
+template <class T>
+__device__ __forceinline__ T* sbase_here(T* p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+// The lane value v, opaque from here on: addresses formed from it again are
+// computed again instead of being kept in registers since their last use.
+__device__ __forceinline__ int here(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
 template <class T>
 __device__ __forceinline__ T* byte_off(T* base, uint32_t ob) {

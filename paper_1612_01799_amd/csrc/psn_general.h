@@ -66,8 +66,12 @@ template <int L, class Real, int STEP>
 struct GCfg {
     static constexpr bool rows = STEP == 1 || STEP == 5;
     static constexpr int FL = L / 2;
-    static constexpr int E = elems_per_thread(FL, rows ? int(sizeof(Real)) : 8);
-    static constexpr int T = FL / E;
+    // (the axis-0 step keeps 12 or 20 elements per thread at n0 = 384 and 320:
+    // 1.07 against 1.33 ms at 384 x 512 x 512 FP32 for 64 threads per line)
+    static constexpr int T = rows ? FL / elems_per_thread(FL, int(sizeof(Real)))
+                             : STEP == 3 && FL >= 256 && mid_plan(FL) ? FL / (4 * odd_part(FL))
+                                                                      : strided_team(FL);
+    static constexpr int E = FL / T;  // elements per thread (the row steps: exactly)
     static constexpr int CX = sizeof(cx<Real>);
     // The axis-0 step at n0 >= 512 reads its stage twiddles from per-stage
     // rows (one row per thread and stage, as P3 does at those sizes), the
@@ -163,8 +167,9 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
         else if constexpr (C::seq) return LdsColsSeq<Real>{sb, B, c};
         else return LdsCols2<Real>{sb, B, c};
     }();
-    cx<Real> d[C::E];          // the row steps' line
-    cx<Real> d2[2][C::E];      // the strided steps' two chains
+    cx<Real> d[Ff::EM];        // the row steps' line
+    static_assert(!rows || (Ff::EI == C::E && Ff::EO == C::E), "every lane of a row step holds E elements");
+    cx<Real> d2[2][Ff::EM];    // the strided steps' two chains
     if constexpr (STEP == 1) {
         // Real row of n2 = FL samples, zero beyond: z_j = x_2j + i x_2j+1
         // (j < FL/2, zero beyond), Z = DFT_FL(z), then the padded spectrum
@@ -203,12 +208,11 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
     } else if constexpr (STEP == 2) {
         const long i0 = ln / hw, k2 = ln % hw;
         const cx<Real>* x = a.w1 + i0 * n1 * hw + k2;
-#pragma unroll
-        for (int e = 0; e < C::E; ++e) {
+        Ff::each_in(t, [&](int e) {
             const int p = Ff::in_pos(t, e);
             d2[0][e] = live ? gld(x + long(p) * hw) : cx<Real>{Real(0), Real(0)};
             d2[1][e] = d2[0][e] * a.tw[2 * p];
-        }
+        });
         Ff::template run<2>(d2, t, tl, lds);
         // output k1 = 2m + chain.  The workgroup's 2 n1 x B outputs are one
         // tile of W2 in each of the 2 n1 / KB k1 blocks, each a run of KB B
@@ -223,23 +227,23 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
         const int run = kb * B;
         constexpr int rounds = C::seq ? 2 : 1;
         constexpr int K1R = 2 * FL / rounds;  // k1 per round
-        constexpr int NQ = K1R / (2 * T);     // stores per lane and round, two elements each
+        constexpr int NQ = (K1R + 2 * T - 1) / (2 * T);  // stores per lane and round, two elements each
 #pragma unroll
         for (int h = 0; h < rounds; ++h) {
             __syncthreads();  // the transform's last exchange (or the last round's stores) read the area
-#pragma unroll
-            for (int e = 0; e < C::E; ++e) {
+            Ff::each_out(t, [&](int e) {
                 const int m = Ff::out_pos(t, e);
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
                     const int k1 = 2 * m + ch - h * K1R;
                     if (k1 >= 0 && k1 < K1R) sb[k1 * B + c] = d2[ch][e];
                 }
-            }
+            });
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < NQ; ++r) {
                 const int q = 2 * int(threadIdx.x) + r * 2 * B * T;  // in this round's area
+                if (K1R % (2 * T) != 0 && q >= K1R * B) break;
                 const int qg = h * K1R * B + q;                         // among the 2 n1 B outputs
                 cx<Real>* y = a.w2 + w2at(i0w, long(qg >> (kbs + __builtin_ctz(B))) * kb, k2w) + (qg & (run - 1));
                 if constexpr (sizeof(Real) == 4) {
@@ -270,14 +274,13 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
         cx<Real>* const xu = a.w2 + w2at(0, k1, k2b);
         const uint32_t xl = (uint32_t(c) + uint32_t(t) * s0) * uint32_t(sizeof(cx<Real>));
         const uint32_t wl = uint32_t(2 * t) * uint32_t(sizeof(cx<Real>));
-        cx<Real> w[C::E];  // w^p of each input position p = t + in_pos(0, e)
-#pragma unroll
-        for (int e = 0; e < C::E; ++e) {
+        cx<Real> w[Ff::EI];  // w^p of each input position p = t + in_pos(0, e)
+        Ff::each_in(t, [&](int e) {
             const int p0 = Ff::in_pos(0, e);
             w[e] = gld(byte_off(sbase(a.tw + 2 * p0), wl));
             d2[0][e] = gld(byte_off(sbase(xu + size_t(p0) * s0), xl));
             d2[1][e] = d2[0][e] * w[e];
-        }
+        });
         if constexpr (C::trows) Ff::template run<2>(d2, t, TwRows<Real>{rows_f}, lds);
         else Ff::template run<2>(d2, t, tl, lds);
         // kernel values of the outputs k0 = 2m + chain, m = t + out_pos(0, e),
@@ -288,13 +291,12 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
         const Real* const Ku = a.K + psn_host::g_k_index(N0, n2, 0, k1f, int(k2b));
         const uint32_t kup = (uint32_t(2 * KT) * uint32_t(t) + uint32_t(c)) * uint32_t(sizeof(Real));
         const uint32_t kdn = (uint32_t(2 * KT) * uint32_t(T - 1 - t) + uint32_t(c)) * uint32_t(sizeof(Real));
-        Real kk[2][C::E];
-#pragma unroll
-        for (int e = 0; e < C::E; ++e)
+        Real kk[2][Ff::EO];
+        Ff::each_out(t, [&](int e) {
 #pragma unroll
             for (int ch = 0; ch < 2; ++ch) {
                 const int a0 = 2 * Ff::out_pos(0, e) + ch;  // k0 of lane t = 0
-                if (a0 + 2 * (T - 1) <= N0) {
+                if (a0 + 2 * Ff::out_last(e) <= N0) {
                     kk[ch][e] = gld(byte_off(sbase(Ku + a0 * KT), kup));
                 } else if (a0 >= N0) {
                     kk[ch][e] = gld(byte_off(sbase(Ku + (2 * N0 - a0 - 2 * (T - 1)) * KT), kdn));
@@ -303,29 +305,28 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
                     kk[ch][e] = Ku[(k0 <= N0 ? k0 : 2 * N0 - k0) * KT + c];
                 }
             }
+        });
         // radices reversed: starts from the forward output layout and ends in
         // its input layout (slot e at position Ff::in_pos(t, e))
         if constexpr (C::trows) Fi::template run_scaled<2>(d2, t, TwRows<Real>{rows_i}, lds, kk);
         else Fi::template run_scaled<2>(d2, t, tl, lds, kk);
-#pragma unroll
-        for (int e = 0; e < C::E; ++e)
+        Ff::each_in(t, [&](int e) {
             gst(byte_off(sbase(xu + size_t(Ff::in_pos(0, e)) * s0), xl), twfma<+1>(d2[1][e], w[e], d2[0][e]));
+        });
     } else if constexpr (STEP == 4) {
         const long i0 = ln / hw, k2 = ln % hw;
         const cx<Real>* x = a.w2;  // input k1 = 2m + chain
-#pragma unroll
-        for (int e = 0; e < C::E; ++e) {
+        Fi::each_in(t, [&](int e) {
             const long m = Fi::in_pos(t, e);
             d2[0][e] = live ? gld(x + w2at(i0, 2 * m, k2)) : cx<Real>{Real(0), Real(0)};
             d2[1][e] = live ? gld(x + w2at(i0, 2 * m + 1, k2)) : cx<Real>{Real(0), Real(0)};
-        }
+        });
         Fi::template run<2>(d2, t, tl, lds);
         cx<Real>* y = a.w1 + i0 * n1 * hw + k2;
-#pragma unroll
-        for (int e = 0; e < C::E; ++e) {
+        Fi::each_out(t, [&](int e) {
             const int p = Fi::out_pos(t, e);
             if (live) gst(y + long(p) * hw, twfma<+1>(d2[1][e], a.tw[2 * p], d2[0][e]));
-        }
+        });
     } else {
         // The row's padded spectrum X[0..FL] is that of a real sequence.  The
         // inverse of length FL of Y[k] = (X[k] + conj X[FL-k])

@@ -74,11 +74,11 @@ constexpr int rows_padded(int N) {
 // lines per workgroup of the contiguous passes (up to `threads` threads);
 // their LDS, at most `lds` bytes, holds the lines and the 2N-entry twiddle table
 constexpr int pick_lines(int N, int T, int cxbytes, int threads, int lds) {
-    int l = threads / T;
-    if (l < 1) l = 1;
-    while (l > 1 && (N % l != 0 || (l * rows_padded(N) + ((2 * N + 15) & ~15)) * cxbytes > lds)) l /= 2;
+    int l = 1;
+    for (int p = 2; p * T <= threads; p *= 2)
+        if (N % p == 0 && (p * rows_padded(N) + ((2 * N + 15) & ~15)) * cxbytes <= lds) l = p;
     if (l * T < 64) {
-        // halving left less than a wave (odd team sizes): any divisor of N that fits
+        // a power of two leaves less than a wave: any divisor of N that fits
         for (int d = threads / T; d > l; --d)
             if (N % d == 0 && (d * rows_padded(N) + ((2 * N + 15) & ~15)) * cxbytes <= lds) return d;
     }
@@ -127,16 +127,24 @@ struct W2Index {
     static constexpr size_t s0 = size_t(N) * KB * (PAIR ? 2 : 1);
 };
 
-// Sizes whose W2 is stored in the paired form.  The axis-0 pass then splits
+// Sizes whose W2 is stored in the paired form, so that the axis-0 pass moves
+// whole 128-byte lines and not halves of them (a bare read, scale and write of
+// W2 in its order is 17-19 % faster so at n = 512).
+// FP32, n a power of two >= 16 or any n >= 256 (PairW2): the axis-0 pass splits
 // each line by decimation in time into its even and odd samples, giving four
-// half-length chains per line; the axis-1 passes take an i0 pair per
-// workgroup.
-// FP32 only: the FP64-arithmetic precisions already move 16 bytes per lane
-// and element, and their paired axis-1 passes measured slower (one 144 KB
-// workgroup per CU then holds two lines per column).
+// half-length chains per line and one 16-byte access per lane; the axis-1
+// passes take an i0 pair per thread.  (n = 384: 1.47 -> 1.37 ms a solve; 96 to
+// 192 measured 5 to 15 % slower so and keep the plain form.)
 template <int N, int DT>
 struct PairW2 {
-    static constexpr bool value = DT == DT_F32 && N >= 16 && (N & (N - 1)) == 0;
+    static constexpr bool value = DT == DT_F32 && (N >= 256 || (N >= 16 && (N & (N - 1)) == 0));
+};
+// FP64 arithmetic, n >= 96 (LaneW2): neighbouring lanes take the two i0 of a
+// pair in every strided pass, on tiles of 4 columns (4 columns x 2 i0 x 16
+// bytes).  n = 512: P2 + P3 + P4 4.93 -> 4.80 ms, n = 256: 0.64 -> 0.60 ms.
+template <int N, int DT>
+struct LaneW2 {
+    static constexpr bool value = DT != DT_F32 && N >= 96;
 };
 
 // W1 layout, tiled over k2: element (i0, i1, k2) lives at
@@ -161,9 +169,10 @@ struct Cfg {
     static constexpr int E = elems_per_thread(N, sizeof(Real));
     static constexpr int T = N / E;
     static constexpr int CX = sizeof(cx<Real>);
-    static constexpr int T24 = N / elems_per_thread(N, 8);                     // P2, P4 team (two chains)
-    static constexpr int BS = pick_cols_p3(N, 8, CX, T24);                     // P2, P4 columns
-    static constexpr int T3 = N / elems_per_thread(N, 8);                      // P3 team (two chains)
+    static constexpr int T24 = strided_team(N);                                // P2, P4 team (two chains)
+    static constexpr int IP = LaneW2<N, DT>::value ? 2 : 1;                    // i0 per P2, P4 workgroup, in neighbouring lanes
+    static constexpr int BS = pick_cols_p3(N, IP == 2 && CX == 16 ? 4 : 8, CX, T24);  // P2, P4 columns
+    static constexpr int T3 = strided_team(N);                                 // P3 team (two chains)
     static constexpr int BP3 = pick_cols_p3_div(N, DT == DT_F32 ? 8 : 4, CX, T3, BS);  // P3 columns (divide BS)
     static_assert(BS % BP3 == 0, "P3 tile must lie inside the W2 layout tile");
     static constexpr int LC = pick_lines(N, T, CX, 512, kMaxLdsRows);          // P1, P5 lines
@@ -254,7 +263,8 @@ p1_r2c(const Batch<DT> bt) {
     const typename C::Io* x = P.rho + (size_t(line0) + ln) * N;
 
     // z[j] = x[2j] + i x[2j+1]; zero for j >= n/2 (the padding)
-    cx<Real> d[F::E];
+    cx<Real> d[F::EM];
+    static_assert(F::EI == F::E && F::EO == F::E, "every lane holds E elements");
 #pragma unroll
     for (int e = 0; e < F::E; ++e) {
         const int pos = F::in_pos(t, e);
@@ -303,20 +313,25 @@ p1_r2c(const Batch<DT> bt) {
 template <class Real, bool SEQ>
 using ChainLds = std::conditional_t<SEQ, LdsColsSeq<Real>, LdsCols2<Real>>;
 
+// Minimum waves per SIMD asked of the compiler for P2 and P4 with em slots per
+// chain and thread (TeamFFT::EM).
+constexpr int p24_waves(int em, bool f32) { return f32 ? 1 : em <= 9 ? 4 : em <= 12 ? 3 : 1; }
+
 template <int N, int DT, int B, int TT, bool SEQ>
-__global__ void __launch_bounds__((B * TT), (SEQ && N / TT <= 8 ? 3 : 1))
+__global__ void __launch_bounds__((Cfg<N, DT>::IP * B * TT),
+                                  (p24_waves(TeamFFT<N, TT, typename Prec<DT>::Real, -1, false>::EM, DT == DT_F32)))
 p2_fwd(const Batch<DT> bt) {
     using C = Cfg<N, DT>;
     using Real = typename C::Real;
     using F = TeamFFT<N, TT, Real, -1, false>;
-    using WI = W2Index<N, Cfg<N, DT>::BS>;
-    static_assert(B == Cfg<N, DT>::BS, "the axis-1 tile is the W2 layout tile");
-    constexpr int E = F::E;
+    constexpr int IP = C::IP, BI = B * IP;  // i0 and lines per workgroup
+    using WI = W2Index<N, C::BS, IP == 2>;
+    static_assert(B == C::BS, "the axis-1 tile is the W2 layout tile");
     constexpr int tiles = N / B;
-    constexpr int units = N * tiles;  // per problem
+    constexpr int units = N / IP * tiles;  // per problem
     extern __shared__ __align__(16) unsigned char smem[];
     cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
-    cx<Real>* stw = sb + (SEQ ? 1 : 2) * B * N;
+    cx<Real>* stw = sb + (SEQ ? 1 : 2) * BI * N;
     const int ug = xcd_unit();
     if (ug >= bt.count * units) return;
     const Prob<DT>& P = bt.p[ug / units];
@@ -324,48 +339,46 @@ p2_fwd(const Batch<DT> bt) {
     const auto& w2 = P.w2;
     const cx<Real>* __restrict__ tw = P.tw;
     const int u = ug % units;
-    const int i0 = u / tiles, tile = u % tiles;
-    const int c = threadIdx.x % B, t = threadIdx.x / B;
-    const int k2 = tile * B + c;
+    const int i0b = u / tiles * IP, tile = u % tiles;
+    const int l = threadIdx.x % BI, t = threadIdx.x / BI;
+    const int i0 = i0b + l % IP, k2 = tile * B + l / IP;
     using W1I = W1Index<N, B>;
 
-    cx<Real> d[2][E], w[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    cx<Real> d[2][F::EM];
+    F::each_in(t, [&](int e) {
         const int pos = F::in_pos(t, e);
         d[0][e] = w1.ld(W1I::at(i0, pos, k2));
-        w[e] = tw[pos];
-    }
+        d[1][e] = tw[pos];
+    });
     TwLds<Real> tl{stw};
-    tl.fill(tw, N, threadIdx.x, B * TT);  // visible after the first exchange
-#pragma unroll
-    for (int e = 0; e < E; ++e) d[1][e] = d[0][e] * w[e];
-    ChainLds<Real, SEQ> lds{sb, B, c};
+    tl.fill(tw, N, threadIdx.x, BI * TT);  // visible after the first exchange
+    F::each_in(t, [&](int e) { d[1][e] = d[0][e] * d[1][e]; });
+    ChainLds<Real, SEQ> lds{sb, BI, l};
     F::template run<2>(d, t, tl, lds);
     {
-        // Stage the workgroup's output in LDS in W2 order (slot-major, B columns
-        // per slot), then store whole runs of KB * B elements, two consecutive
-        // elements per lane.  The two-chain exchange area holds all 2N slots;
-        // the one-chain area holds N, so that variant stages in two rounds.
-        constexpr int KB = WI::KB, RUN = KB * B;
+        // Stage the workgroup's output in LDS in W2 order (slot-major, BI
+        // elements per slot), then store whole runs of KB * BI elements, two
+        // consecutive elements per lane.  The two-chain exchange area holds all
+        // 2N slots; the one-chain area holds N, so that variant stages in two
+        // rounds.
+        constexpr int KB = WI::KB, RUN = KB * BI;
         constexpr int HALF = SEQ ? N : 2 * N;  // slots per round
-        static_assert((HALF * B) % RUN == 0, "rounds cover whole runs");
-        const size_t tile0 = WI::at(i0, 0, tile * B);  // (slot 0, column tile*B): start of block 0's run
+        const size_t tile0 = WI::at(i0b, 0, tile * B);  // (slot 0, column tile*B): start of block 0's run
 #pragma unroll
         for (int h = 0; h < 2 * N / HALF; ++h) {
             __syncthreads();  // the last exchange's (or round's) reads are done
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int m = F::out_pos(t, e);
+            const int th = here(t);
+            F::each_out(th, [&](int e) {
+                const int m = F::out_pos(th, e);
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
                     const int sl = WI::slot(2 * m + ch) - h * HALF;
-                    if (sl >= 0 && sl < HALF) sb[sl * B + c] = d[ch][e];
+                    if (sl >= 0 && sl < HALF) sb[sl * BI + l] = d[ch][e];
                 }
-            }
+            });
             __syncthreads();
-            for (int g = 2 * int(threadIdx.x); g < HALF * B; g += 2 * B * TT) {
-                const int gg = h * HALF * B + g;
+            for (int g = 2 * int(threadIdx.x); g < HALF * BI; g += 2 * BI * TT) {
+                const int gg = h * HALF * BI + g;
                 w2.st2(tile0 + size_t(gg / RUN) * WI::blk + gg % RUN, sb[g], sb[g + 1]);
             }
         }
@@ -390,31 +403,29 @@ struct P3Rows {
     static constexpr bool value = N >= 512;
 };
 
-// Minimum waves per SIMD asked of the compiler for P3.  The one-chain variant
-// uses little LDS, so it asks for three waves per SIMD (six for 512-thread
-// FP32 workgroups with up to 8 elements per thread: three workgroups per CU).
-// FP32 keeps few values live across the forward transform (see kLean), so
-// this holds up to 20 elements per thread; FP64 arithmetic only up to 8.
-// Longer plans are left unbounded, where a bound would only force spills.
-constexpr int p3_waves(int e, int threads, bool f32, bool seq) {
-    if (!seq || e > (f32 ? 20 : 8)) return 1;
-    return f32 && threads > 256 && e <= 8 ? 6 : 3;
+// Minimum waves per SIMD asked of the compiler for P3 with em slots per chain
+// and thread (TeamFFT::EM): what fits without spills.
+constexpr int p3_waves(int em, bool f32) {
+    if (f32) return em <= 9 ? 6 : em <= 10 ? 5 : em <= 12 ? 4 : em <= 20 ? 3 : 1;
+    return em <= 9 ? 4 : em <= 12 ? 3 : 1;
 }
 
 template <int N, int DT, int B, int TT, int SL, bool SEQ>
-__global__ void __launch_bounds__((B * TT * SL), (p3_waves(N / TT, B * TT * SL, DT == DT_F32, SEQ)))
+__global__ void __launch_bounds__((B * TT * SL),
+                                  (p3_waves(TeamFFT<N, TT, typename Prec<DT>::Real, -1, false>::EM, DT == DT_F32)))
 p3_conv(const Batch<DT> bt) {
     using C = Cfg<N, DT>;
     using Real = typename C::Real;
     using Ff = TeamFFT<N, TT, Real, -1, false>;
     using Fi = TeamFFT<N, TT, Real, +1, true>;
     static_assert(SL == 1 || SL == 2, "one row or a row pair per workgroup");
-    constexpr int E = Ff::E;
     constexpr int tiles = N / B;
     constexpr int units = (2 / SL) * N * tiles;  // per problem
-    using WI = W2Index<N, Cfg<N, DT>::BS>;
-    static_assert(Cfg<N, DT>::BS % B == 0, "the axis-0 tile lies inside a W2 layout tile");
-    constexpr size_t s0 = WI::s0;  // stride of i0 in W2
+    constexpr int IP = C::IP;                    // consecutive i0 in neighbouring lanes
+    using WI = W2Index<N, C::BS, IP == 2>;
+    static_assert(C::BS % B == 0, "the axis-0 tile lies inside a W2 layout tile");
+    static_assert(TT % IP == 0 && (N / Ff::R0) % IP == 0, "an i0 pair is two neighbouring threads of a line");
+    constexpr size_t s0 = WI::s0;  // stride of i0 (of i0 pairs) in W2
     extern __shared__ __align__(16) unsigned char smem[];
     cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
     cx<Real>* stw = sb + (SEQ ? 1 : 2) * B * SL * N;
@@ -435,20 +446,22 @@ p3_conv(const Batch<DT> bt) {
     } else {
         q = u / tiles;
         tile = u % tiles;
-        set = (threadIdx.x / B) & 1;
+        set = (threadIdx.x / (B * IP)) & 1;
     }
-    const int c = threadIdx.x % B, t = threadIdx.x / (B * SL);
+    // lanes run over i0 % IP, the columns, the rows and the rest of i0
+    const int par = threadIdx.x % IP, c = (threadIdx.x / IP) % B;
+    const int tp = threadIdx.x / (IP * B * SL), t = IP * tp + par;
     const int k2 = tile * B + c;
     // Addresses: a base uniform over the workgroup (row q, column tile * B)
-    // plus a 32-bit lane offset.  Row M-q sits BS elements after row q in the
-    // W2 layout; its kernel row is q as well, except for the pair (0, n).
+    // plus a 32-bit lane offset.  Row M-q sits IP * BS elements after row q in
+    // the W2 layout; its kernel row is q as well, except for the pair (0, n).
     static_assert(WI::s0 * N * sizeof(cx<double>) < (size_t(1) << 32) &&
                       size_t(N + 1) * (N + 1) * N * sizeof(double) < (size_t(1) << 32),
                   "lane byte offsets fit 32 bits");
     const size_t ub = WI::at(0, q, tile * B);
     // element e sits at the uniform base xb(e) plus the lane offset xl
-    const uint32_t xl = uint32_t(c) + uint32_t(set) * Cfg<N, DT>::BS + uint32_t(t) * uint32_t(s0);
-    auto xb = [&](int e) { return ub + size_t(Ff::in_pos(0, e)) * s0; };
+    const uint32_t xl = uint32_t(IP * c + par) + uint32_t(set * IP) * C::BS + uint32_t(tp) * uint32_t(s0);
+    auto xb = [&](int e) { return ub + size_t(Ff::in_pos(0, e) / IP) * s0; };
     // Kernel values of the even and odd outputs a = 2m, b = 2m + 1 of
     // m = out_pos(t, e) = t + m0(e), at the folded index min(a, 2N - a) of
     // this lane's kernel row (plane q, or n for the set-1 row of pair 0) in the
@@ -456,71 +469,59 @@ p3_conv(const Batch<DT> bt) {
     // whole element lies on one side of n, the folded index is a constant plus
     // 2t or minus 2t: a uniform base plus one of two lane offsets.
     constexpr int KT = psn_host::k_tile(N);
-    const typename C::Kt* __restrict__ Kq = K;
     const uint32_t kl = uint32_t(psn_host::k_index(N, (set != 0 && q == 0) ? N : q, 0, k2));
     const uint32_t kup = (kl + uint32_t(2 * t * KT)) * uint32_t(sizeof(typename C::Kt));
     const uint32_t kdn = (kl + uint32_t(2 * (TT - 1 - t) * KT)) * uint32_t(sizeof(typename C::Kt));
     auto kval = [&](int e, int odd) -> Real {
         const int m0 = Ff::out_pos(0, e);
-        if (2 * m0 + 2 * TT - 1 <= N) return Real(gld(byte_off(sbase(Kq + (2 * m0 + odd) * KT), kup)));
-        if (2 * m0 >= N) return Real(gld(byte_off(sbase(Kq + (2 * N - 2 * m0 - odd - 2 * (TT - 1)) * KT), kdn)));
+        if (2 * (m0 + Ff::out_last(e)) + 1 <= N) return Real(gld(byte_off(sbase(K + (2 * m0 + odd) * KT), kup)));
+        if (2 * m0 >= N) return Real(gld(byte_off(sbase(K + (2 * N - 2 * m0 - odd - 2 * (TT - 1)) * KT), kdn)));
         const int a = 2 * (m0 + t) + odd;
-        return Real(gld(Kq + kl + uint32_t(a <= N ? a : 2 * N - a) * KT));
+        return Real(gld(K + kl + uint32_t(a <= N ? a : 2 * N - a) * KT));
+    };
+    // w^i0 of slot e's input position, which is its output position too
+    auto pre = [&](int e) {
+        return gld(byte_off(sbase_here(tw + Ff::in_pos(0, e)), uint32_t(t) * uint32_t(C::CX)));
     };
 
-    cx<Real> x[E], w[E];
-    Real kk[2][E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        x[e] = w2.ld(xb(e), xl);
-        w[e] = tw[Ff::in_pos(t, e)];
-    }
-    // FP32 variants with the one-chain exchange or more than 8 elements per
-    // thread keep fewer values live across the forward transform (more waves
-    // fit): they load the kernel values after it and reload the twiddles w at
-    // the end.  The FP64-arithmetic variants measured faster with early loads.
-    constexpr bool kLean = DT == DT_F32 && (SEQ || E > 8);
-    auto load_k = [&]() {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            kk[0][e] = kval(e, 0);
-            kk[1][e] = kval(e, 1);
-        }
-    };
-    if constexpr (!kLean) load_k();
+    static_assert(Ff::EM == Fi::EM, "same plan, reversed");
+    cx<Real> d[2][Ff::EM];
+    Ff::each_in(t, [&](int e) {
+        d[0][e] = w2.ld(xb(e), xl);
+        d[1][e] = pre(e);
+    });
     // Stage twiddles: per-stage rows of both transforms (shared when their
     // radices match) for n >= 512, where the saved index arithmetic outweighs
     // the scattered reads that fill them; else the swizzled 2N-entry table.
     constexpr bool kRows = P3Rows<N>::value;
     cx<Real>* rows_i = stw + (Ff::template same_rows<Fi>() ? 0 : Ff::rows_size());
-    TwLds<Real> tl{stw};
+    using Tw = std::conditional_t<kRows, TwRows<Real>, TwLds<Real>>;
     if constexpr (kRows) {
         Ff::fill_rows(stw, tw, threadIdx.x, B * TT * SL);  // visible after the first exchange
         if constexpr (!Ff::template same_rows<Fi>()) Fi::fill_rows(rows_i, tw, threadIdx.x, B * TT * SL);
     } else {
-        tl.fill(tw, N, threadIdx.x, B * TT * SL);
+        TwLds<Real>{stw}.fill(tw, N, threadIdx.x, B * TT * SL);
     }
-
-    cx<Real> d[2][E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        d[0][e] = x[e];
-        d[1][e] = x[e] * w[e];
-    }
-    ChainLds<Real, SEQ> lds{sb, B * SL, int(threadIdx.x % (B * SL))};
-    if constexpr (kRows) Ff::template run<2>(d, t, TwRows<Real>{stw}, lds);
-    else Ff::template run<2>(d, t, tl, lds);
-    if constexpr (kLean) load_k();
+    Ff::each_in(t, [&](int e) { d[1][e] = d[0][e] * d[1][e]; });
+    ChainLds<Real, SEQ> lds{sb, B * SL, c + B * set * (SL - 1)};
+    // Few values stay live across the transforms, so that more waves fit: the
+    // kernel values are loaded after the forward one, the twiddles w again at
+    // the end, and the addresses of the exchanges are formed anew for the
+    // inverse (here) instead of being kept.  n = 512 FP64: 166 -> 126 VGPRs,
+    // four waves per SIMD instead of three, 2.55 -> 2.39 ms; n = 320 FP64:
+    // 212 -> 146, three instead of two.
+    Ff::template run<2>(d, t, Tw{stw}, lds);
+    __builtin_amdgcn_sched_barrier(0);
+    Real kk[2][Ff::EO];
+    Ff::each_out(t, [&](int e) {
+        kk[0][e] = kval(e, 0);
+        kk[1][e] = kval(e, 1);
+    });
     // the multiply by K is folded into the first stage of the inverse
-    if constexpr (kRows) Fi::template run_scaled<2>(d, t, TwRows<Real>{rows_i}, lds, kk);
-    else Fi::template run_scaled<2>(d, t, tl, lds, kk);
-    if constexpr (kLean) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) w[e] = gld(byte_off(sbase(tw + Ff::in_pos(0, e)), uint32_t(t) * uint32_t(C::CX)));
-    }
+    Fi::template run_scaled<2>(d, here(t), Tw{kRows ? rows_i : stw}, lds, kk);
+    __builtin_amdgcn_sched_barrier(0);
     if (k2 != 0) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) w2.st(xb(e), xl, twfma<+1>(d[1][e], w[e], d[0][e]));
+        Ff::each_in(t, [&](int e) { w2.st(xb(e), xl, twfma<+1>(d[1][e], pre(e), d[0][e])); });
     }
 }
 
@@ -548,7 +549,7 @@ p3_col0(const Batch<DT> bt) {
     using G0 = Col0<N, DT>;
     using Ff = TeamFFT<N, G0::T, Real, -1, false>;
     using Fi = TeamFFT<N, G0::T, Real, +1, true>;
-    using WI = W2Index<N, Cfg<N, DT>::BS, PairW2<N, DT>::value>;
+    using WI = W2Index<N, Cfg<N, DT>::BS, PairW2<N, DT>::value || LaneW2<N, DT>::value>;
     extern __shared__ __align__(16) unsigned char smem[];
 
     if (int(blockIdx.x) >= bt.count * G0::groups) return;
@@ -570,39 +571,34 @@ p3_col0(const Batch<DT> bt) {
     const typename C::Kt* Krow = K + psn_host::k_index(N, kt1, 0, 0);  // column 0 of plane kt1
     const typename C::Kt* Kbr = Kb + size_t(kt1) * (N + 1);
 
-    cx<Real> x[Ff::E], acc[Ff::E];
-#pragma unroll
-    for (int e = 0; e < Ff::E; ++e) x[e] = w2.ld(WI::at(Ff::in_pos(t, e), k1, 0));
+    static_assert(Ff::EM == Fi::EM, "same plan, reversed");
+    cx<Real> x[Ff::EI], acc[Ff::EI];
+    Ff::each_in(t, [&](int e) { x[e] = w2.ld(WI::at(Ff::in_pos(t, e), k1, 0)); });
     LdsCols<Real> lds{sb + set, 2, 0};
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
-        cx<Real> d[Ff::E];
-#pragma unroll
-        for (int e = 0; e < Ff::E; ++e) d[e] = p ? x[e] * tw[Ff::in_pos(t, e)] : x[e];
+        cx<Real> d[Ff::EM];
+        Ff::each_in(t, [&](int e) { d[e] = p ? x[e] * tw[Ff::in_pos(t, e)] : x[e]; });
         Ff::run(d, t, tw, lds);
         __syncthreads();
-#pragma unroll
-        for (int e = 0; e < Ff::E; ++e) sb[set * N + Ff::out_pos(t, e)] = d[e];
+        Ff::each_out(t, [&](int e) { sb[set * N + Ff::out_pos(t, e)] = d[e]; });
         __syncthreads();
-#pragma unroll
-        for (int e = 0; e < Ff::E; ++e) {
+        Ff::each_out(t, [&](int e) {
             const int m = Ff::out_pos(t, e);
             const int k0 = 2 * m + p;
             const int kt0 = k0 <= N ? k0 : 2 * N - k0;
             const int mp = p == 0 ? (m == 0 ? 0 : N - m) : N - 1 - m;
             const cx<Real> zp = conj(sb[partner * N + mp]);
             d[e] = scale(d[e], Real(Krow[size_t(kt0) * psn_host::k_tile(N)])) + scale(zp, Real(Kbr[kt0]));
-        }
+        });
         Fi::run(d, t, tw, lds);
-#pragma unroll
-        for (int e = 0; e < Ff::E; ++e) {
+        Fi::each_out(t, [&](int e) {
             if (p == 0) acc[e] = d[e];
             else acc[e] = acc[e] + mul_conj(d[e], tw[Fi::out_pos(t, e)]);
-        }
+        });
     }
     if (live) {
-#pragma unroll
-        for (int e = 0; e < Ff::E; ++e) w2.st(WI::at(Fi::out_pos(t, e), k1, 0), acc[e]);
+        Fi::each_out(t, [&](int e) { w2.st(WI::at(Fi::out_pos(t, e), k1, 0), acc[e]); });
     }
 }
 
@@ -610,19 +606,20 @@ p3_col0(const Batch<DT> bt) {
 // Unit = (i0, tile of B columns k2).  The even and odd rows of a line are
 // inverted in lockstep and combined as y = y_even + w^-j y_odd.
 template <int N, int DT, int B, int TT, bool SEQ>
-__global__ void __launch_bounds__((B * TT), (SEQ && N / TT <= 8 ? 3 : 1))
+__global__ void __launch_bounds__((Cfg<N, DT>::IP * B * TT),
+                                  (p24_waves(TeamFFT<N, TT, typename Prec<DT>::Real, +1, false>::EM, DT == DT_F32)))
 p4_inv(const Batch<DT> bt) {
     using C = Cfg<N, DT>;
     using Real = typename C::Real;
     using F = TeamFFT<N, TT, Real, +1, false>;
-    using WI = W2Index<N, Cfg<N, DT>::BS>;
-    static_assert(B == Cfg<N, DT>::BS, "the axis-1 tile is the W2 layout tile");
-    constexpr int E = F::E;
+    constexpr int IP = C::IP, BI = B * IP;  // i0 and lines per workgroup
+    using WI = W2Index<N, C::BS, IP == 2>;
+    static_assert(B == C::BS, "the axis-1 tile is the W2 layout tile");
     constexpr int tiles = N / B;
-    constexpr int units = N * tiles;  // per problem
+    constexpr int units = N / IP * tiles;  // per problem
     extern __shared__ __align__(16) unsigned char smem[];
     cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
-    cx<Real>* stw = sb + (SEQ ? 1 : 2) * B * N;
+    cx<Real>* stw = sb + (SEQ ? 1 : 2) * BI * N;
     const int ug = xcd_unit();
     if (ug >= bt.count * units) return;
     const Prob<DT>& P = bt.p[ug / units];
@@ -630,26 +627,23 @@ p4_inv(const Batch<DT> bt) {
     const auto& w2 = P.w2;
     const cx<Real>* __restrict__ tw = P.tw;
     const int u = ug % units;
-    const int i0 = u / tiles, tile = u % tiles;
-    const int c = threadIdx.x % B, t = threadIdx.x / B;
-    const int k2 = tile * B + c;
+    const int l = threadIdx.x % BI, t = threadIdx.x / BI;
+    const int i0 = u / tiles * IP + l % IP, k2 = u % tiles * B + l / IP;
     using W1I = W1Index<N, B>;
 
-    cx<Real> d[2][E], w[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    cx<Real> d[2][F::EM];
+    F::each_in(t, [&](int e) {
         const int pos = F::in_pos(t, e);
         d[0][e] = w2.ld(WI::at(i0, 2 * pos, k2));
         d[1][e] = w2.ld(WI::at(i0, 2 * pos + 1, k2));
-        w[e] = tw[F::out_pos(t, e)];
-    }
+    });
     TwLds<Real> tl{stw};
-    tl.fill(tw, N, threadIdx.x, B * TT);  // visible after the first exchange
-    ChainLds<Real, SEQ> lds{sb, B, c};
+    tl.fill(tw, N, threadIdx.x, BI * TT);  // visible after the first exchange
+    ChainLds<Real, SEQ> lds{sb, BI, l};
     F::template run<2>(d, t, tl, lds);
-#pragma unroll
-    for (int e = 0; e < E; ++e)
-        w1.st(W1I::at(i0, F::out_pos(t, e), k2), twfma<+1>(d[1][e], w[e], d[0][e]));
+    const int to = here(t);
+    F::each_out(to, [&](int e) { w1.st(W1I::at(i0, F::out_pos(to, e), k2),
+                  twfma<+1>(d[1][e], gld(byte_off(sbase(tw + F::out_pos(0, e)), uint32_t(to) * uint32_t(C::CX))), d[0][e])); });
 }
 
 // ------------------------------------------------------------------ paired W2
@@ -671,7 +665,6 @@ p2p_fwd(const Batch<DT> bt) {
     using F = TeamFFT<N, TT, Real, -1, false>;
     using WI = W2Index<N, C::BS, true>;
     static_assert(B == C::BS, "the axis-1 tile is the W2 layout tile");
-    constexpr int E = F::E;
     constexpr int tiles = N / B;
     constexpr int units = (N / 2) * tiles;  // per problem
     extern __shared__ __align__(16) unsigned char smem[];
@@ -689,42 +682,37 @@ p2p_fwd(const Batch<DT> bt) {
     const int k2 = tile * B + c;
     using W1I = W1Index<N, B>;
 
-    cx<Real> xa[E], xb[E], w[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    cx<Real> xa[F::EI], xb[F::EI], w[F::EI];
+    F::each_in(t, [&](int e) {
         const int pos = F::in_pos(t, e);
         xa[e] = w1.ld(W1I::at(2 * pr, pos, k2));
         xb[e] = w1.ld(W1I::at(2 * pr + 1, pos, k2));
         w[e] = tw[pos];
-    }
+    });
     TwLds<Real> tl{stw};
     tl.fill(tw, N, threadIdx.x, B * TT);  // visible after the first exchange
     ChainLds<Real, SEQ> lds{sb, B, c};
-    cx<Real> ra[2][E], d[2][E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    cx<Real> ra[2][F::EM], d[2][F::EM];
+    F::each_in(t, [&](int e) {
         ra[0][e] = xa[e];
         ra[1][e] = xa[e] * w[e];
-    }
+    });
     F::template run<2>(ra, t, tl, lds);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    F::each_in(t, [&](int e) {
         d[0][e] = xb[e];
         d[1][e] = xb[e] * w[e];
-    }
+    });
     F::template run<2>(d, t, tl, lds);
     {
         // Stage in rounds of HALF slots: element (slot, column, i0 parity) at
         // ((slot - h HALF) B + c) 2 + parity, the order of the W2 runs.
         constexpr int KB = WI::KB, RUN = 2 * KB * B;
         constexpr int HALF = SEQ ? N / 2 : N;  // slots per round
-        static_assert((2 * HALF * B) % RUN == 0, "rounds cover whole runs");
         const size_t tile0 = WI::at(2 * pr, 0, tile * B);  // start of block 0's run
 #pragma unroll
         for (int h = 0; h < 2 * N / HALF; ++h) {
             __syncthreads();  // the last exchange's (or round's) reads are done
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
+            F::each_out(t, [&](int e) {
                 const int m = F::out_pos(t, e);
 #pragma unroll
                 for (int ch = 0; ch < 2; ++ch) {
@@ -734,7 +722,7 @@ p2p_fwd(const Batch<DT> bt) {
                         sb[(sl * B + c) * 2 + 1] = d[ch][e];
                     }
                 }
-            }
+            });
             __syncthreads();
             for (int g = 2 * int(threadIdx.x); g < 2 * HALF * B; g += 2 * B * TT) {
                 const int gg = h * 2 * HALF * B + g;
@@ -784,7 +772,6 @@ p3p_conv(const Batch<DT> bt) {
     using Fi = TeamFFT<H, TT, Real, +1, true>;
     static_assert(SL == 1 || SL == 2, "one row or a row pair per workgroup");
     static_assert(G == 4 || G == 2, "four chains exchanged all at once or two at a time");
-    constexpr int E = Ff::E;
     constexpr int tiles = N / B;
     constexpr int units = (2 / SL) * N * tiles;  // per problem
     using WI = W2Index<N, C::BS, true>;
@@ -822,9 +809,9 @@ p3p_conv(const Batch<DT> bt) {
     const uint32_t xl = uint32_t(2 * c) + uint32_t(set) * (2 * C::BS) + uint32_t(t) * uint32_t(sp);
     auto xb = [&](int e) { return ub + size_t(Ff::in_pos(0, e)) * sp; };
 
-    cx<Real> d[4][E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) w2.ld_pair(xb(e), xl, d[0][e], d[1][e]);
+    static_assert(Ff::EM == Fi::EM, "same plan, reversed");
+    cx<Real> d[4][Ff::EM];
+    Ff::each_in(t, [&](int e) { w2.ld_pair(xb(e), xl, d[0][e], d[1][e]); });
     // kernel values of outputs 2m, 2m+1 (m = out_pos(t, e) = t + m0) and of
     // their partners n - 2m, n - 2m - 1: a uniform base plus one of two lane
     // offsets in the tiled K row (plane q, or n for the set-1 row of pair 0)
@@ -852,20 +839,18 @@ p3p_conv(const Batch<DT> bt) {
         if constexpr (Ff::S == 1) __syncthreads();  // no exchange: the combine reads the table
     }
     // pre-twiddles w^2i, w^(2i+1) of the pair this lane holds
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    Ff::each_in(t, [&](int e) {
         const int i = Ff::in_pos(t, e);
         d[2][e] = d[0][e] * gld(tw + 2 * i);
         d[3][e] = d[1][e] * gld(tw + 2 * i + 1);
-    }
+    });
     using Lds = std::conditional_t<G == 4, LdsColsN<Real, 4>, LdsColsSeq<Real, 2>>;
     Lds lds{sb, B * SL, int(threadIdx.x % (B * SL))};
     if constexpr (G == 4) lds.plane = 2 * H * B * SL;
     TwHalf<Real> th{tl};
     if constexpr (kRows) Ff::template run<4>(d, t, TwRows<Real>{stw}, lds);
     else Ff::template run<4>(d, t, th, lds);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    Ff::each_out(t, [&](int e) {
         const int m = Ff::out_pos(t, e);
         // w^2m = exp(-2 pi i m / n)
         const cx<Real> W = kRows ? gld(byte_off(sbase(tw + 2 * Ff::out_pos(0, e)), uint32_t(2 * t * C::CX)))
@@ -880,17 +865,16 @@ p3p_conv(const Batch<DT> bt) {
             d[2 * odd][e] = {fmad(ks, a.x, fmad(kw.x, b.x, -kw.y * b.y)), fmad(ks, a.y, fmad(kw.x, b.y, kw.y * b.x))};
             d[2 * odd + 1][e] = {fmad(ks, b.x, fmad(kw.x, a.x, kw.y * a.y)), fmad(ks, b.y, fmad(kw.x, a.y, -kw.y * a.x))};
         }
-    }
+    });
     if constexpr (kRows) Fi::template run<4>(d, t, TwRows<Real>{rows_i}, lds);
     else Fi::template run<4>(d, t, th, lds);
     if (k2 != 0) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
+        Fi::each_out(t, [&](int e) {
             const int i = Fi::out_pos(t, e);
             const cx<Real> u0 = twfma<+1>(d[2][e], gld(tw + 2 * i), d[0][e]);
             const cx<Real> u1 = twfma<+1>(d[3][e], gld(tw + 2 * i + 1), d[1][e]);
             w2.st_pair(xb(e), xl, u0, u1);
-        }
+        });
     }
 }
 
@@ -906,7 +890,6 @@ p4p_inv(const Batch<DT> bt) {
     using F = TeamFFT<N, TT, Real, +1, false>;
     using WI = W2Index<N, C::BS, true>;
     static_assert(B == C::BS, "the axis-1 tile is the W2 layout tile");
-    constexpr int E = F::E;
     constexpr int tiles = N / B;
     constexpr int units = (N / 2) * tiles;  // per problem
     extern __shared__ __align__(16) unsigned char smem[];
@@ -924,30 +907,28 @@ p4p_inv(const Batch<DT> bt) {
     const int k2 = tile * B + c;
     using W1I = W1Index<N, B>;
 
-    cx<Real> a[2][E], b[2][E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    cx<Real> a[2][F::EM], b[2][F::EM];
+    F::each_in(t, [&](int e) {
         const int pos = F::in_pos(t, e);
         w2.ld_pair(WI::at(2 * pr, 2 * pos, k2), a[0][e], b[0][e]);
         w2.ld_pair(WI::at(2 * pr, 2 * pos + 1, k2), a[1][e], b[1][e]);
-    }
+    });
     TwLds<Real> tl{stw};
     tl.fill(tw, N, threadIdx.x, B * TT);  // visible after the first exchange
     if constexpr (F::S == 1) __syncthreads();  // no exchange: the combine reads the table
     ChainLds<Real, SEQ> lds{sb, B, c};
     // the combine twiddles w^-j come from the LDS table (fewer live registers)
     F::template run<2>(a, t, tl, lds);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
+    F::each_out(t, [&](int e) {
         const int j = F::out_pos(t, e);
         w1.st(W1I::at(2 * pr, j, k2), twfma<+1>(a[1][e], tl(j), a[0][e]));
-    }
-    F::template run<2>(b, t, tl, lds);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int j = F::out_pos(t, e);
+    });
+    const int tb = here(t);  // the addresses of the second line are formed anew: no spills at 128 VGPRs
+    F::template run<2>(b, tb, tl, lds);
+    F::each_out(tb, [&](int e) {
+        const int j = F::out_pos(tb, e);
         w1.st(W1I::at(2 * pr + 1, j, k2), twfma<+1>(b[1][e], tl(j), b[0][e]));
-    }
+    });
 }
 
 // ------------------------------------------------------------------ P5
@@ -983,7 +964,8 @@ p5_c2r(const Batch<DT> bt) {
     TwLds<Real> tl{sb + C::LC * C::NP};
     tl.fill(tw, N, threadIdx.x, C::LC * C::T);
     using TO = TileOrder<N, C::LC, C::T, BL>;
-    cx<Real> d[F::E];
+    cx<Real> d[F::EM];
+    static_assert(F::EI == F::E && F::EO == F::E, "every lane holds E elements");
 #pragma unroll
     for (int q = 0; q < F::E; ++q) {
         int lj, k0, off;
@@ -1031,63 +1013,55 @@ inline bool allow_lds(const void* fn, size_t bytes) {
 
 // ------------------------------------------------------------------ schedules
 // Tile shapes of the strided passes: B adjacent columns per workgroup, TT
-// threads per line.  Each pass has three compiled candidates; the autotuner
+// threads per line.  Each pass has four compiled candidates; the autotuner
 // times them once per (n, precision) and keeps the fastest.  A candidate that
 // does not fit (LDS, threads, radix plan) is replaced by candidate 0.
+//   P2/P4 (they keep the W2 layout tile, B = BS), n a power of two or below 48:
+//     the two chains exchanged together, twice the elements per thread (an odd
+//     factor: half), the chains one after the other, four elements; n >= 48
+//     with an odd factor, the chains always one after the other but for the
+//     third: 8 elements on a power-of-two team, on N / 8 threads, together, and
+//     all odd factors in every thread (12 or 20 elements).
+//   P3: one row with the chains one after the other; the row pair k1, M-k1; the
+//     chains together (odd factor: 12 or 20 elements, the row pair, which is the
+//     fastest for many densities per launch: 13 of 160^3 FP32 0.51 against
+//     0.54 ms, while one density takes 67 against 51 us); four elements (odd
+//     factor: 8 on N / 8 threads).
+// The one-chain exchange stages the W2 runs of P2 in two rounds of n slots.
 struct TileV {
     int B, TT;
     int SL = 1;        // rows per workgroup (the axis-0 pass only)
     bool SEQ = false;  // exchange the two chains one at a time (half the LDS)
 };
 
-constexpr bool tile_ok(int N, TileV v, int cxbytes) {
-    return v.B >= 1 && v.TT >= 1 && (v.SL == 1 || v.SL == 2) && N % v.B == 0 && N % v.TT == 0 &&
-           v.B * v.TT * v.SL <= 1024 &&
-           ((v.SEQ ? 1 : 2) * v.B * v.SL * N + ((2 * N + 15) & ~15)) * cxbytes <= kMaxLdsP3 &&
-           make_plan(N, N / v.TT).n > 0 && N / v.TT <= 20;
-}
-
-constexpr TileV pick_tile(int N, TileV v, TileV dflt, int cxbytes) { return tile_ok(N, v, cxbytes) ? v : dflt; }
-constexpr TileV pick_tile3(int N, TileV v, TileV dflt, int cxbytes, int layout_tile) {
-    return (tile_ok(N, v, cxbytes) && layout_tile % v.B == 0) ? v : dflt;
+// ip: i0 per workgroup of the axis-1 passes; the axis-0 pass has SL rows per
+// workgroup instead and its teams split into i0 pairs (ip = 2)
+constexpr bool tile_ok(int N, TileV v, int cxbytes, int ip, bool axis0) {
+    const int lines = v.B * (axis0 ? v.SL : ip);
+    return v.B >= 1 && v.TT >= 1 && (v.SL == 1 || v.SL == 2) && N % v.B == 0 && v.TT <= N && (mid_plan(N) || N % v.TT == 0) &&
+           lines * v.TT <= 1024 && ((v.SEQ ? 1 : 2) * lines * N + ((2 * N + 15) & ~15)) * cxbytes <= kMaxLdsP3 &&
+           (!axis0 || v.TT % ip == 0) && team_plan(N, N / v.TT).n > 0 && N / v.TT <= 20;
+    
 }
 
 template <int N, int DT>
 struct Sched {
     using C = Cfg<N, DT>;
-    static constexpr int e8 = elems_per_thread(N, 8), e16 = elems_per_thread(N, 4);
-    static constexpr TileV d24{C::BS, C::T24}, d3{C::BP3, C::T3};
-    // P2/P4 keep the W2 layout tile (B = BS); P3 tiles must divide it
-    // Sizes with a factor 3 or 5 keep all odd factors in every thread, so their
-    // teams are small (8 threads for a 160-point line); their second candidate
-    // halves the elements per thread instead (twice the threads per line, a
-    // longer radix plan).
-    static constexpr int odd = N / (N & -N);
-    static constexpr int eh = odd * 2;
-    // (the one-chain exchange stages the W2 runs in two rounds of n slots,
-    // which needs the k1 block to divide n)
-    // The fourth candidate: sizes with an odd factor halve the elements per
-    // thread and exchange one chain at a time; powers of two take 4 elements
-    // per thread (twice the threads, one more exchange).
-    static constexpr bool seq_ok = N % psn_host::w2_k1_block(N) == 0;
+    static constexpr TileV d24{C::BS, C::T24, 1, mid_plan(N) || C::IP == 2}, d3{C::BP3, C::T3, 1, true};
+    static constexpr int odd = odd_part(N);
+    static constexpr bool mid = mid_plan(N);
+    static constexpr int e16 = odd > 1 ? odd * 2 : elems_per_thread(N, 4), eo = odd * 4;
+    static constexpr int tm = N / elems_per_thread(N, 8);
+    static constexpr TileV pick24(TileV v) { return tile_ok(N, v, C::CX, C::IP, false) ? v : d24; }
+    static constexpr TileV pick3(TileV v) { return tile_ok(N, v, C::CX, C::IP, true) && C::BS % v.B == 0 ? v : d3; }
     static constexpr TileV v24[psn_host::kScheduleCandidates] = {
-        d24, pick_tile(N, odd > 1 ? TileV{C::BS, N / eh} : TileV{C::BS, N / e16}, d24, C::CX),
-        seq_ok ? pick_tile(N, {C::BS, C::T24, 1, true}, d24, C::CX) : d24,
-        odd > 1 ? (seq_ok ? pick_tile(N, TileV{C::BS, N / eh, 1, true}, d24, C::CX) : d24)
-                : pick_tile(N, TileV{C::BS, N / 4}, d24, C::CX)};
-    // P3: one row per workgroup; the row pair k1, M-k1 per workgroup (sizes with
-    // an odd factor: with the chains exchanged one at a time); one row with
-    // the chains exchanged one at a time; and (odd factor) half the elements
-    // per thread, or (powers of two) 4 elements per thread with the one-chain
-    // exchange.  (The whole layout tile of 8 columns with the one-chain
-    // exchange fits one 512-thread FP64-arithmetic workgroup per CU and
-    // measured 30 % slower at n = 512.)
+        d24, pick24(mid ? TileV{C::BS, tm, 1, true} : TileV{C::BS, N / e16}),
+        pick24(TileV{C::BS, C::T24, 1, !d24.SEQ}),
+        pick24(mid ? TileV{C::BS, N / eo, 1, true} : TileV{C::BS, N / (odd > 1 ? eo : 4)})};
     static constexpr TileV v3[psn_host::kScheduleCandidates] = {
-        d3,
-        pick_tile3(N, odd > 1 ? TileV{C::BP3, C::T3, 2, true} : TileV{C::BP3, C::T3, 2}, d3, C::CX, C::BS),
-        pick_tile3(N, {C::BP3, C::T3, 1, true}, d3, C::CX, C::BS),
-        pick_tile3(N, odd > 1 ? TileV{C::BP3, N / eh} : TileV{C::BP3, N / 4, 1, true}, d3, C::CX, C::BS)};
-    static_assert(tile_ok(N, d24, C::CX) && tile_ok(N, d3, C::CX), "default tiles must fit");
+        d3, pick3(TileV{C::BP3, C::T3, 2, true}), pick3(mid ? TileV{C::BP3, N / eo, 2, true} : TileV{C::BP3, C::T3}),
+        pick3(mid ? TileV{C::BP3, tm, 1, true} : TileV{C::BP3, N / (odd > 1 ? odd * 2 : 4), 1, true})};
+    static_assert(tile_ok(N, d24, C::CX, C::IP, false) && tile_ok(N, d3, C::CX, C::IP, true), "default tiles must fit");
 };
 
 // Axis-0 tiles on the paired layout: B columns, TT threads per half line
@@ -1100,9 +1074,9 @@ struct TileP {
 
 constexpr bool tilep_ok(int N, TileP v, int cxbytes) {
     return v.B >= 1 && v.TT >= 1 && (v.SL == 1 || v.SL == 2) && (v.G == 2 || v.G == 4) && N % v.B == 0 &&
-           (N / 2) % v.TT == 0 && v.B * v.TT * v.SL <= 1024 &&
+           (mid_plan(N / 2) || (N / 2) % v.TT == 0) && v.B * v.TT * v.SL <= 1024 &&
            (size_t(v.G) * (N / 2) * v.B * v.SL + ((2 * N + 15) & ~15)) * cxbytes <= size_t(kMaxLdsP3) &&
-           make_plan(N / 2, N / 2 / v.TT).n > 0 && N / 2 / v.TT <= 16;
+           team_plan(N / 2, N / 2 / v.TT).n > 0 && N / 2 / v.TT <= 16;
 }
 constexpr TileP pick_tilep(int N, TileP v, TileP dflt, int cxbytes, int layout_tile) {
     return (tilep_ok(N, v, cxbytes) && layout_tile % v.B == 0) ? v : dflt;
@@ -1112,25 +1086,27 @@ template <int N, int DT>
 struct SchedP {
     using C = Cfg<N, DT>;
     static constexpr int H = N / 2;
-    static constexpr int e8 = H >= 8 ? 8 : H;
-    static constexpr int e4 = H >= 4 ? 4 : H;
+    static constexpr int T = strided_team(H);
+    static constexpr int e4 = H >= 4 ? 4 : H, e16 = H >= 16 ? 16 : H;
     // eight points per chain and thread, two chains per exchange round (all
     // four at once halves the workgroups per CU and measured 45 % slower at
     // n = 512); the row pair k1, M-k1 per workgroup; four points per chain
-    // (twice the threads, one more exchange); sixteen points per chain (one
-    // exchange fewer, half the threads)
-    static constexpr int e16 = H >= 16 ? 16 : H;
-    static constexpr TileP d3{C::BP3, H / e8, 1, 2};
+    // (twice the threads, one more exchange; with an odd factor: no idle
+    // threads in the outer stages instead); sixteen points per chain (one
+    // exchange fewer, half the threads; with an odd factor: the same, and the
+    // row pair)
+    static constexpr TileP d3{C::BP3, T, 1, 2};
     static constexpr TileP v3[psn_host::kScheduleCandidates] = {
-        d3, pick_tilep(N, TileP{C::BP3, H / e8, 2, 2}, d3, C::CX, C::BS),
-        pick_tilep(N, TileP{C::BP3, H / e4, 1, 2}, d3, C::CX, C::BS),
-        pick_tilep(N, TileP{C::BP3, H / e16, 1, 2}, d3, C::CX, C::BS)};
+        d3, pick_tilep(N, TileP{C::BP3, T, 2, 2}, d3, C::CX, C::BS),
+        pick_tilep(N, TileP{C::BP3, mid_plan(H) ? H / elems_per_thread(H, 8) : H / e4, 1, 2}, d3, C::CX, C::BS),
+        pick_tilep(N, mid_plan(H) ? TileP{C::BP3, H / elems_per_thread(H, 8), 2, 2} : TileP{C::BP3, H / e16, 1, 2}, d3,
+                   C::CX, C::BS)};
 };
 
 // LDS of the strided passes: the exchange area plus the stage twiddle rows
 template <int N, int DT, int B, int TT, bool SEQ>
 constexpr size_t lds_p24() {
-    return (size_t(SEQ ? 1 : 2) * B * N + TwLds<typename Cfg<N, DT>::Real>::slots(N)) * Cfg<N, DT>::CX;
+    return (size_t(SEQ ? 1 : 2) * Cfg<N, DT>::IP * B * N + TwLds<typename Cfg<N, DT>::Real>::slots(N)) * Cfg<N, DT>::CX;
 }
 template <int N, int DT, int B, int TT, int SL, bool SEQ>
 constexpr size_t lds_p3() {
@@ -1148,8 +1124,8 @@ hipError_t launch_p2(const Batch<DT>& bt, hipStream_t s) {
     const size_t lds = lds_p24<N, DT, v.B, v.TT, v.SEQ>();
     static const bool ok = allow_lds(reinterpret_cast<const void*>(&p2_fwd<N, DT, v.B, v.TT, v.SEQ>), lds);
     if (!ok) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((p2_fwd<N, DT, v.B, v.TT, v.SEQ>), dim3(xcd_grid(long(bt.count) * N * (N / v.B))), dim3(v.B * v.TT),
-                       lds, s, bt);
+    hipLaunchKernelGGL((p2_fwd<N, DT, v.B, v.TT, v.SEQ>), dim3(xcd_grid(long(bt.count) * (N / Cfg<N, DT>::IP) * (N / v.B))),
+                       dim3(Cfg<N, DT>::IP * v.B * v.TT), lds, s, bt);
     return hipSuccess;
 }
 
@@ -1159,8 +1135,8 @@ hipError_t launch_p4(const Batch<DT>& bt, hipStream_t s) {
     const size_t lds = lds_p24<N, DT, v.B, v.TT, v.SEQ>();
     static const bool ok = allow_lds(reinterpret_cast<const void*>(&p4_inv<N, DT, v.B, v.TT, v.SEQ>), lds);
     if (!ok) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((p4_inv<N, DT, v.B, v.TT, v.SEQ>), dim3(xcd_grid(long(bt.count) * N * (N / v.B))), dim3(v.B * v.TT),
-                       lds, s, bt);
+    hipLaunchKernelGGL((p4_inv<N, DT, v.B, v.TT, v.SEQ>), dim3(xcd_grid(long(bt.count) * (N / Cfg<N, DT>::IP) * (N / v.B))),
+                       dim3(Cfg<N, DT>::IP * v.B * v.TT), lds, s, bt);
     return hipSuccess;
 }
 
