@@ -198,7 +198,8 @@ psn_status psn_solve_batched_noalloc(int count, psn_plan *const *plans,
  * pass and after each of the five passes (P1 axis-2 real-to-complex, P2
  * axis-1 forward, P3 axis-0 forward x K inverse, P4 axis-1 inverse, P5 axis-2
  * complex-to-real), waits for the stream, and writes the five pass durations
- * in milliseconds to pass_ms[5].  For measurement only (it synchronises).
+ * in milliseconds to pass_ms[5].  Cubes of n <= 64 run P2, P3 and P4 as one
+ * launch, which is timed as P3.  For measurement only (it synchronises).
  * Errors: as psn_solve. */
 psn_status psn_solve_timed(psn_plan *p, const void *rho, void *u, void *stream, double *pass_ms);
 
@@ -206,7 +207,8 @@ psn_status psn_solve_timed(psn_plan *p, const void *rho, void *u, void *stream, 
  * p3 (0..3) for the axis-0 pass.  Every candidate computes the same
  * transform; results agree within rounding but not bitwise, since a
  * candidate may run another radix plan or another order of operations.  For
- * one candidate the result is bitwise reproducible.  Errors: PSN_EINVAL. */
+ * one candidate the result is bitwise reproducible.  Cubes of n <= 64 have one
+ * form of these passes, whatever the candidate.  Errors: PSN_EINVAL. */
 psn_status psn_plan_set_schedule(psn_plan *p, int p24, int p3);
 
 /* Choose how the near-zone correction enters (psn_correction); call before

@@ -130,14 +130,14 @@ struct W2Index {
 // Sizes whose W2 is stored in the paired form, so that the axis-0 pass moves
 // whole 128-byte lines and not halves of them (a bare read, scale and write of
 // W2 in its order is 17-19 % faster so at n = 512).
-// FP32, n a power of two >= 16 or any n >= 256 (PairW2): the axis-0 pass splits
+// FP32, n = 128 and n >= 256 (PairW2): the axis-0 pass splits
 // each line by decimation in time into its even and odd samples, giving four
 // half-length chains per line and one 16-byte access per lane; the axis-1
 // passes take an i0 pair per thread.  (n = 384: 1.47 -> 1.37 ms a solve; 96 to
 // 192 measured 5 to 15 % slower so and keep the plain form.)
 template <int N, int DT>
 struct PairW2 {
-    static constexpr bool value = DT == DT_F32 && (N >= 256 || (N >= 16 && (N & (N - 1)) == 0));
+    static constexpr bool value = DT == DT_F32 && (N >= 256 || N == 128);
 };
 // FP64 arithmetic, n >= 96 (LaneW2): neighbouring lanes take the two i0 of a
 // pair in every strided pass, on tiles of 4 columns (4 columns x 2 i0 x 16
@@ -160,6 +160,30 @@ struct W1Index {
     }
 };
 
+// Cubes whose axes 1 and 0 run plane by plane in one launch (plane_conv): three
+// launches a solve instead of six, up to n = 64.  One FP32 density: n = 32
+// 26 -> 15.5 us, n = 48 29 -> 19.5, n = 64 34 -> 23; FP64 35 -> 21 at n = 48,
+// 39 -> 30 at n = 64; 13 densities a launch 95 -> 85 us (n = 64 FP32).  At n = 96
+// FP32 one density still gains (57 -> 52 us), but a CU holds one workgroup of a
+// plane only, and 13 take 384 us instead of 279.
+template <int N, int DT>
+struct PlaneCfg {
+    using Real = typename Prec<DT>::Real;
+    static constexpr int CX = sizeof(cx<Real>);
+    // 8 elements per thread, or 12 with a factor 3 (two stages for 48 points and
+    // not three: plane_conv 18.4 -> 12.6 us in FP64)
+    static constexpr int T = N / (odd_part(N) > 1 ? 4 * odd_part(N) : elems_per_thread(N, 8));
+    static constexpr int threads = N * T;
+    static constexpr int pitch() {
+        int p = LdsLine<Real>::slots(N);
+        while (p % 16 != 8) ++p;
+        return p;
+    }
+    static constexpr size_t lds = size_t(N * pitch() + TwLds<Real>::slots(N)) * CX;
+    static constexpr bool value = N <= 64;
+    static_assert(!value || (threads <= 1024 && lds <= size_t(kMaxLdsP3)), "a plane fits a workgroup");
+};
+
 template <int N, int DT>
 struct Cfg {
     using P = Prec<DT>;
@@ -171,7 +195,7 @@ struct Cfg {
     static constexpr int CX = sizeof(cx<Real>);
     static constexpr int T24 = strided_team(N);                                // P2, P4 team (two chains)
     static constexpr int IP = LaneW2<N, DT>::value ? 2 : 1;                    // i0 per P2, P4 workgroup, in neighbouring lanes
-    static constexpr int BS = pick_cols_p3(N, IP == 2 && CX == 16 ? 4 : 8, CX, T24);  // P2, P4 columns
+    static constexpr int BS = PlaneCfg<N, DT>::value ? 1 : pick_cols_p3(N, IP == 2 && CX == 16 ? 4 : 8, CX, T24);  // P2, P4 columns
     static constexpr int T3 = strided_team(N);                                 // P3 team (two chains)
     static constexpr int BP3 = pick_cols_p3_div(N, DT == DT_F32 ? 8 : 4, CX, T3, BS);  // P3 columns (divide BS)
     static_assert(BS % BP3 == 0, "P3 tile must lie inside the W2 layout tile");
@@ -931,6 +955,103 @@ p4p_inv(const Batch<DT> bt) {
     });
 }
 
+// ------------------------------------------------------------------ small cubes
+// Axes 1 and 0 of one k2 plane in one launch, for small n (PlaneCfg): a workgroup
+// holds the n x n plane of one k2 and the outputs k1 = 2m + p of one parity p in
+// LDS, rows m; what the five passes do in P2, P3, column 0 and P4.  The two
+// parities' inverses along axis 1 go to the two halves of W2 as [p][i0][k2][i1]
+// and P5 adds them, so that 2n workgroups share a plane's work (n would leave
+// most CUs idle) and none waits for another.  Latency bound: few waves, a chain
+// of 8 to 10 exchanges; the kernel values are loaded first of all.
+//   1  line i0 along i1: DFT_n(x w^(p i1)), written to row m, column i0
+//   2  row m along i0: both parities of k0, x K, inverse, back to row m
+//      (k2 = 0, the packed column: Z' = a Z(k) + b conj(Z(-k)), the partner row
+//      and position read from LDS, as in p3_col0)
+//   3  line i0 along m: inverse, times w^-(p i1)
+// A row's own LDS is the exchange area of the team that has it; the row pitch
+// of 8 mod 16 spreads a column's accesses over the banks.
+template <int N, int DT>
+__global__ void __launch_bounds__((PlaneCfg<N, DT>::threads)) plane_conv(const Batch<DT> bt) {
+    using PC = PlaneCfg<N, DT>;
+    using Real = typename PC::Real;
+    using Kt = typename Prec<DT>::Kt;
+    constexpr int T = PC::T, LP = PC::pitch();
+    using Ff = TeamFFT<N, T, Real, -1, false>;
+    using Fr = TeamFFT<N, T, Real, +1, true>;   // starts from Ff's output layout
+    using Fi = TeamFFT<N, T, Real, +1, false>;
+    constexpr int KT = psn_host::k_tile(N);
+    extern __shared__ __align__(16) unsigned char smem[];
+    cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
+    const int ug = xcd_unit();
+    constexpr int units = 2 * N;  // per problem
+    if (ug >= bt.count * units) return;  // whole workgroup
+    const Prob<DT>& P = bt.p[ug / units];
+    const cx<Real>* __restrict__ tw = P.tw;
+    const int u = ug % units, k2 = u >> 1, p = u & 1;
+    const int t = threadIdx.x % T, ln = threadIdx.x / T;  // ln: i0 in steps 1 and 3, m in step 2
+    const size_t line = (size_t(ln) * N + k2) * N;        // of W1 and of W2's halves
+
+    cx<Real> a[1][Ff::EM];
+    Ff::each_in(t, [&](int e) { a[0][e] = P.w1.ld(line + Ff::in_pos(t, e)); });
+    TwLds<Real> tl{sb + N * LP};
+    tl.fill(tw, N, threadIdx.x, PC::threads);  // visible after the first barrier
+    static_assert(LdsLine<Real>::slots(N) <= LP, "a padded line fits its row");
+    LdsLine<Real> row{sb + ln * LP};
+    if (p) Ff::each_in(t, [&](int e) { a[0][e] = a[0][e] * gld(tw + Ff::in_pos(t, e)); });
+    Ff::template run<1>(a, t, tl, row);
+    __syncthreads();  // the last exchange's reads are done
+    Ff::each_out(t, [&](int e) { sb[Ff::out_pos(t, e) * LP + ln] = a[0][e]; });
+    __syncthreads();
+
+    const int k1 = 2 * ln + p, k1f = k1 <= N ? k1 : 2 * N - k1;
+    const Kt* const Krow = P.K + psn_host::k_index(N, k1f, 0, k2);
+    auto fold = [](int k) { return k <= N ? k : 2 * N - k; };
+    Real kk[2][Ff::EO];
+    Ff::each_out(t, [&](int e) {
+        const int m = Ff::out_pos(t, e);
+        kk[0][e] = Real(gld(Krow + fold(2 * m) * KT));
+        kk[1][e] = Real(gld(Krow + fold(2 * m + 1) * KT));
+    });
+    cx<Real> d[2][Ff::EM];
+    Ff::each_in(t, [&](int e) {
+        const int i = Ff::in_pos(t, e);
+        d[0][e] = sb[ln * LP + i];
+        d[1][e] = d[0][e] * tl(i);
+    });
+    Ff::template run<2>(d, here(t), tl, row);
+    if (k2 == 0) {  // whole workgroup
+        const Kt* const Kbr = P.Kb + size_t(k1f) * (N + 1);
+        const int pm = p ? N - 1 - ln : (N - ln) % N;  // row of -k1
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            __syncthreads();
+            Ff::each_out(t, [&](int e) { sb[ln * LP + Ff::out_pos(t, e)] = d[q][e]; });
+            __syncthreads();
+            Ff::each_out(t, [&](int e) {
+                const int m = Ff::out_pos(t, e);
+                const cx<Real> z = conj(sb[pm * LP + (q ? N - 1 - m : (N - m) % N)]);
+                d[q][e] = scale(d[q][e], kk[q][e]) + scale(z, Real(gld(Kbr + fold(2 * m + q))));
+                kk[q][e] = Real(1);
+            });
+        }
+    }
+    Fr::template run_scaled<2>(d, here(t), tl, row, kk);
+    __syncthreads();  // the last exchange's reads are done
+    Ff::each_in(t, [&](int e) {
+        const int i = Ff::in_pos(t, e);
+        sb[ln * LP + i] = twfma<+1>(d[1][e], tl(i), d[0][e]);
+    });
+    __syncthreads();
+
+    Fi::each_in(t, [&](int e) { a[0][e] = sb[Fi::in_pos(t, e) * LP + ln]; });
+    Fi::template run<1>(a, here(t), tl, row);  // its first exchange waits for every line's loads
+    const size_t out = size_t(p) * N * N * N + line;
+    Fi::each_out(t, [&](int e) {
+        const int i = Fi::out_pos(t, e);
+        P.w2.st(out + i, p ? mul_conj(a[0][e], tl(i)) : a[0][e]);
+    });
+}
+
 // ------------------------------------------------------------------ P5
 template <int N, int DT>
 __global__ void __launch_bounds__((Cfg<N, DT>::LC * Cfg<N, DT>::T))
@@ -970,7 +1091,9 @@ p5_c2r(const Batch<DT> bt) {
     for (int q = 0; q < F::E; ++q) {
         int lj, k0, off;
         TO::at(int(threadIdx.x), q, lj, k0, off);
-        d[q] = w1.ld(W1I::at(i0, i1b + lj, k0 + off));
+        const size_t i = W1I::at(i0, i1b + lj, k0 + off);
+        if constexpr (PlaneCfg<N, DT>::value) d[q] = P.w2.ld(i) + P.w2.ld(size_t(N) * N * N + i);
+        else d[q] = w1.ld(i);
     }
 #pragma unroll
     for (int q = 0; q < F::E; ++q) {
@@ -1227,8 +1350,8 @@ hipError_t launch_p3v(const Batch<DT>& bt, hipStream_t s, int v) {
     }
 }
 
-// Enqueue the six kernels of one solve for bt.count problems of size N with
-// schedule (v24 for P2/P4, v3 for P3).
+// Enqueue the kernels of one solve (six; three for PlaneCfg sizes) for bt.count
+// problems of size N with schedule (v24 for P2/P4, v3 for P3).
 template <int N, int DT>
 hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, int v3) {
     using C = Cfg<N, DT>;
@@ -1241,18 +1364,28 @@ hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, 
     static const bool lds_ok = allow_lds(reinterpret_cast<const void*>(&p1_r2c<N, DT>), lds_rows) &&
                                allow_lds(reinterpret_cast<const void*>(&p5_c2r<N, DT>), lds_rows);
     if (!lds_ok) return hipErrorInvalidValue;
-    hipError_t e;
+    [[maybe_unused]] hipError_t e;
     mark(0);
     hipLaunchKernelGGL((p1_r2c<N, DT>), dim3(xcd_grid(cnt * N * N / C::LC)), dim3(C::LC * C::T), lds_rows, s, bt);
     mark(1);
-    if ((e = launch_p24<N, DT>(bt, s, v24, true)) != hipSuccess) return e;
-    mark(2);
-    if ((e = launch_p3v<N, DT>(bt, s, v3)) != hipSuccess) return e;
-    using G0 = Col0<N, DT>;
-    hipLaunchKernelGGL((p3_col0<N, DT>), dim3(cnt * G0::groups), dim3(2 * G0::T * G0::G), G0::lds, s, bt);
-    mark(3);
-    if ((e = launch_p24<N, DT>(bt, s, v24, false)) != hipSuccess) return e;
-    mark(4);
+    if constexpr (PlaneCfg<N, DT>::value) {
+        using PC = PlaneCfg<N, DT>;
+        static const bool ok = allow_lds(reinterpret_cast<const void*>(&plane_conv<N, DT>), PC::lds);
+        if (!ok) return hipErrorInvalidConfiguration;
+        mark(2);
+        hipLaunchKernelGGL((plane_conv<N, DT>), dim3(xcd_grid(cnt * 2 * N)), dim3(PC::threads), PC::lds, s, bt);
+        mark(3);
+        mark(4);
+    } else {
+        if ((e = launch_p24<N, DT>(bt, s, v24, true)) != hipSuccess) return e;
+        mark(2);
+        if ((e = launch_p3v<N, DT>(bt, s, v3)) != hipSuccess) return e;
+        using G0 = Col0<N, DT>;
+        hipLaunchKernelGGL((p3_col0<N, DT>), dim3(cnt * G0::groups), dim3(2 * G0::T * G0::G), G0::lds, s, bt);
+        mark(3);
+        if ((e = launch_p24<N, DT>(bt, s, v24, false)) != hipSuccess) return e;
+        mark(4);
+    }
     hipLaunchKernelGGL((p5_c2r<N, DT>), dim3(xcd_grid(cnt * N * N / C::LC)), dim3(C::LC * C::T), lds_rows, s, bt);
     mark(5);
     return hipGetLastError();
@@ -1262,6 +1395,10 @@ hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, 
 // (contents are irrelevant to the timing) and return the fastest indices.
 template <int N, int DT>
 hipError_t tune_n(const Batch<DT>& bt, hipStream_t s, int* best24, int* best3) {
+    *best24 = *best3 = 0;
+    if constexpr (PlaneCfg<N, DT>::value) {
+        return hipSuccess;  // one schedule
+    } else {
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t e = hipEventCreate(&a);
     if (e == hipSuccess) e = hipEventCreate(&b);
@@ -1296,13 +1433,12 @@ hipError_t tune_n(const Batch<DT>& bt, hipStream_t s, int* best24, int* best3) {
     if (a) (void)hipEventDestroy(a);
     if (b) (void)hipEventDestroy(b);
     if (e != hipSuccess) return e;
-    *best24 = 0;
-    *best3 = 0;
     for (int v = 1; v < NC; ++v) {
         if (t24[v] < 0.97f * t24[*best24]) *best24 = v;
         if (t3[v] < 0.97f * t3[*best3]) *best3 = v;
     }
     return hipSuccess;
+    }
 }
 
 template <int DT>
