@@ -381,8 +381,10 @@ constexpr int strided_team(int N) {
 template <class Real>
 struct TwGlobal {
     static constexpr bool kRows = false;
-    const cx<Real>* __restrict__ p;
-    __device__ __forceinline__ cx<Real> operator()(int m) const { return p[m]; }
+    const cx<Real>* __restrict__ p;  // uniform: one 32-bit lane offset per load
+    __device__ __forceinline__ cx<Real> operator()(int m) const {
+        return *reinterpret_cast<const cx<Real>*>(reinterpret_cast<const char*>(p) + uint32_t(m) * uint32_t(sizeof(cx<Real>)));
+    }
 };
 // LDS copy of the table, entries permuted within aligned blocks of 16 (XOR
 // swizzle, no padding): the stage twiddles one wave reads are multiples of a

@@ -237,9 +237,10 @@ struct Batch {
 // Workgroup ids are dealt to the XCDs round robin; give each XCD a contiguous
 // run of units so neighbouring tiles (which may share 128-byte lines) meet in
 // the same L2.
-__device__ __forceinline__ int xcd_unit() {
-    const int g = blockIdx.x;
-    return (g % 8) * (gridDim.x / 8) + g / 8;
+// `first` blocks (a multiple of 8) before the units do other work.
+__device__ __forceinline__ int xcd_unit(int first = 0) {
+    const int g = int(blockIdx.x) - first;
+    return (g % 8) * ((int(gridDim.x) - first) / 8) + g / 8;
 }
 
 // Grid size for `units` units dealt by xcd_unit().
@@ -421,11 +422,129 @@ p2_fwd(const Batch<DT> bt) {
 // same L2.  All global loads (data, the pre/post twiddles of the odd chain and
 // the kernel values) are issued before any arithmetic; the stage twiddles come
 // from a copy of the table in LDS.  Column 0 (the packed k2 = 0 / k2 = n pair)
-// is left to p3_col0.
+// is col0_conv's, on workgroups of the same launch.
 template <int N>
 struct P3Rows {
     static constexpr bool value = N >= 512;
 };
+
+// LDS of P3: the exchange area plus the stage twiddles
+template <int N, int DT, int B, int TT, int SL, bool SEQ>
+constexpr size_t lds_p3() {
+    using Real = typename Cfg<N, DT>::Real;
+    using Ff = TeamFFT<N, TT, Real, -1, false>;
+    using Fi = TeamFFT<N, TT, Real, +1, true>;
+    const size_t rows = P3Rows<N>::value ? Ff::rows_size() + (Ff::template same_rows<Fi>() ? 0 : Fi::rows_size())
+                                         : TwLds<Real>::slots(N);
+    return (size_t(SEQ ? 1 : 2) * B * SL * N + rows) * Cfg<N, DT>::CX;
+}
+
+// Per-stage twiddle rows for the half-length transforms of the paired middle
+// pass (n >= 512, where the saved index arithmetic outweighs the fill).
+template <int N>
+struct P3PRows {
+    static constexpr bool value = N >= 512;
+};
+template <int N, int DT, int TT>
+constexpr size_t p3p_tw_entries() {
+    using Real = typename Cfg<N, DT>::Real;
+    using Ff = TeamFFT<N / 2, TT, Real, -1, false>;
+    using Fi = TeamFFT<N / 2, TT, Real, +1, true>;
+    if constexpr (P3PRows<N>::value) return Ff::rows_size() + (Ff::template same_rows<Fi>() ? 0 : Fi::rows_size());
+    else return TwLds<Real>::slots(N);
+}
+
+template <int N, int DT, int B, int TT, int SL, int G>
+constexpr size_t lds_p3p() {
+    return (size_t(G) * (N / 2) * B * SL + p3p_tw_entries<N, DT, TT>()) * Cfg<N, DT>::CX;
+}
+
+// Column 0 of W2 carries Z = A + iB with A, B the spectra of the real k2 = 0
+// and k2 = n planes.  With the partner row -k the product is
+// Z' = a Z(k) + b conj(Z(-k)), a = (K0+Kn)/2 (stored in K's column 0) and
+// b = (K0-Kn)/2 (stored in Kb).  A row pair is rows q and M-q (row 0 pairs
+// with itself, as does row n).  It is a short dependent chain over few
+// workgroups and 128-byte lines of 8 used bytes, so it runs as the first
+// workgroups of P3's own launch (of NT threads and LDS bytes, G row pairs each) beside the
+// other columns, and not as a launch of its own.  One density: n = 96 FP32 55 ->
+// 49 us, n = 128 67 -> 62, n = 96 FP64 73 -> 68, n = 128 112 -> 106, n = 162 248 ->
+// 233; the axis-0 pass and column 0 at n = 256 FP32 160 -> 154, n = 512 1160 -> 1145.
+// The other columns' workgroups neither read nor write column 0.
+template <int N, int DT, int NT, size_t LDS>
+struct Col0 {
+    // a row pair has four teams, one for each row and parity of k0 (one team that
+    // took both parities needed 30 registers more than P3 has in FP64)
+    static constexpr int T = 4 * Cfg<N, DT>::T3 <= NT ? Cfg<N, DT>::T3 : mid_plan(N) ? N / elems_per_thread(N, 8) : NT / 4;
+    // row pairs that the threads and that the LDS hold; threads past the last
+    // pair only join the barriers, on one more region of LDS
+    static constexpr int gt = NT / (4 * T), gl = int(LDS / (size_t(4) * N * Cfg<N, DT>::CX));
+    static constexpr int G = gt * 4 * T == NT && gt <= gl ? gt : gt < gl - 1 ? gt : gl - 1;
+    static_assert(G >= 1, "a workgroup holds a row pair");
+    static constexpr int groups = (N + G - 1) / G;  // workgroups per problem
+    static __host__ __device__ __forceinline__ int blocks(int count) { return (count * groups + 7) / 8 * 8; }
+};
+
+template <int N, int DT, int NT, size_t LDS>
+__device__ __forceinline__ void col0_conv(const Batch<DT>& bt, int blk, void* smem) {
+    using C = Cfg<N, DT>;
+    using Real = typename C::Real;
+    using Kt = typename C::Kt;
+    using G0 = Col0<N, DT, NT, LDS>;
+    using Ff = TeamFFT<N, G0::T, Real, -1, false>;
+    using Fi = TeamFFT<N, G0::T, Real, +1, true>;
+    using WI = W2Index<N, C::BS, PairW2<N, DT>::value || LaneW2<N, DT>::value>;
+    static_assert(Ff::EM == Fi::EM, "same plan, reversed");
+    if (blk >= bt.count * G0::groups) return;  // whole workgroup
+    const Prob<DT>& P = bt.p[blk / G0::groups];
+    const auto& w2 = P.w2;
+    const cx<Real>* __restrict__ tw = P.tw;
+    const int g = threadIdx.x / (4 * G0::T);  // row pair within the workgroup
+    const int set = threadIdx.x & 1, p = (threadIdx.x >> 1) & 1;
+    const int t = (threadIdx.x >> 2) % G0::T;
+    const int qg = (blk % G0::groups) * G0::G + g;
+    const bool live = g < G0::G && qg < N;  // the last workgroup may hold pairs past the end
+    const int q = live ? qg : N - 1;
+    cx<Real>* sb = static_cast<cx<Real>*>(smem) + size_t(g < G0::G ? g : G0::G) * 4 * N;
+    const int k1 = set == 0 ? q : (q == 0 ? N : 2 * N - q);
+    const int kt1 = (q == 0) ? (set ? N : 0) : q;
+    const int partner = (q == 0) ? set : 1 - set;
+    const uint32_t kr = uint32_t(psn_host::k_index(N, kt1, 0, 0)), kb = uint32_t(kt1) * (N + 1);  // plane kt1, column 0
+
+    cx<Real> d[Ff::EM];
+    Ff::each_in(t, [&](int e) { d[e] = w2.ld(WI::at(Ff::in_pos(t, e), k1, 0)); });
+    if (p) Ff::each_in(t, [&](int e) { d[e] = d[e] * gld(tw + Ff::in_pos(t, e)); });
+    LdsCols<Real> lds{sb + set + 2 * p, 4, 0};
+    Ff::run(d, t, tw, lds);
+    __syncthreads();
+    Ff::each_out(t, [&](int e) { sb[(set + 2 * p) * N + Ff::out_pos(t, e)] = d[e]; });
+    __syncthreads();
+    Ff::each_out(t, [&](int e) {
+        const int m = Ff::out_pos(t, e);
+        const int k0 = 2 * m + p;
+        const int kt0 = k0 <= N ? k0 : 2 * N - k0;
+        const int mp = p == 0 ? (m == 0 ? 0 : N - m) : N - 1 - m;
+        const cx<Real> zp = conj(sb[(partner + 2 * p) * N + mp]);
+        const Real a = Real(gld(byte_off(P.K, (kr + uint32_t(kt0 * psn_host::k_tile(N))) * uint32_t(sizeof(Kt)))));
+        const Real b = Real(gld(byte_off(P.Kb, (kb + uint32_t(kt0)) * uint32_t(sizeof(Kt)))));
+        d[e] = scale(d[e], a) + scale(zp, b);
+    });
+    Fi::run(d, here(t), tw, lds);
+    const int to = here(t);
+    __syncthreads();
+    if (p) {
+        Fi::each_out(to, [&](int e) {
+            const int i = Fi::out_pos(to, e);
+            sb[set * N + i] = mul_conj(d[e], gld(tw + i));
+        });
+    }
+    __syncthreads();
+    if (live && p == 0) {
+        Fi::each_out(to, [&](int e) {
+            const int i = Fi::out_pos(to, e);
+            w2.st(WI::at(i, k1, 0), d[e] + sb[set * N + i]);
+        });
+    }
+}
 
 // Minimum waves per SIMD asked of the compiler for P3 with em slots per chain
 // and thread (TeamFFT::EM): what fits without spills.
@@ -454,7 +573,10 @@ p3_conv(const Batch<DT> bt) {
     cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
     cx<Real>* stw = sb + (SEQ ? 1 : 2) * B * SL * N;
 
-    const int ug = xcd_unit();
+    constexpr size_t lds_bytes = lds_p3<N, DT, B, TT, SL, SEQ>();
+    const int first = Col0<N, DT, B * TT * SL, lds_bytes>::blocks(bt.count);
+    if (int(blockIdx.x) < first) return col0_conv<N, DT, B * TT * SL, lds_bytes>(bt, int(blockIdx.x), smem);
+    const int ug = xcd_unit(first);
     if (ug >= bt.count * units) return;  // whole workgroup
     const Prob<DT>& P = bt.p[ug / units];
     const auto& w2 = P.w2;
@@ -483,8 +605,9 @@ p3_conv(const Batch<DT> bt) {
                       size_t(N + 1) * (N + 1) * N * sizeof(double) < (size_t(1) << 32),
                   "lane byte offsets fit 32 bits");
     const size_t ub = WI::at(0, q, tile * B);
-    // element e sits at the uniform base xb(e) plus the lane offset xl
-    const uint32_t xl = uint32_t(IP * c + par) + uint32_t(set * IP) * C::BS + uint32_t(tp) * uint32_t(s0);
+    // element e sits at the uniform base xb(e) plus the lane offset xl (the lanes
+    // of column 0, which col0_conv has, take column 1's and store nothing)
+    const uint32_t xl = uint32_t(IP * (k2 == 0 ? 1 : c) + par) + uint32_t(set * IP) * C::BS + uint32_t(tp) * uint32_t(s0);
     auto xb = [&](int e) { return ub + size_t(Ff::in_pos(0, e) / IP) * s0; };
     // Kernel values of the even and odd outputs a = 2m, b = 2m + 1 of
     // m = out_pos(t, e) = t + m0(e), at the folded index min(a, 2N - a) of
@@ -546,83 +669,6 @@ p3_conv(const Batch<DT> bt) {
     __builtin_amdgcn_sched_barrier(0);
     if (k2 != 0) {
         Ff::each_in(t, [&](int e) { w2.st(xb(e), xl, twfma<+1>(d[1][e], pre(e), d[0][e])); });
-    }
-}
-
-// Column 0 of W2 carries Z = A + iB with A, B the spectra of the real k2 = 0
-// and k2 = n planes.  With the partner row -k the product is
-// Z' = a Z(k) + b conj(Z(-k)), a = (K0+Kn)/2 (stored in K's column 0) and
-// b = (K0-Kn)/2 (stored in Kb).  A row pair is rows q and M-q (row 0 pairs
-// with itself, as does row n); a workgroup holds Col0::G row pairs so that
-// short lines still fill a 64-lane wave.
-template <int N, int DT>
-struct Col0 {
-    // the team of the strided passes (at most 8 elements per thread, twice
-    // the threads of the row passes' team at n = 512: 25.8 -> 22.4 us there)
-    static constexpr int T = Cfg<N, DT>::T3;
-    static constexpr int G = 2 * T >= 64 ? 1 : (64 / (2 * T) < N ? 64 / (2 * T) : N);  // row pairs per workgroup
-    static constexpr int groups = (N + G - 1) / G;                                    // workgroups per problem
-    static constexpr size_t lds = size_t(G) * 2 * N * Cfg<N, DT>::CX;
-};
-
-template <int N, int DT>
-__global__ void __launch_bounds__((2 * Col0<N, DT>::T * Col0<N, DT>::G))
-p3_col0(const Batch<DT> bt) {
-    using C = Cfg<N, DT>;
-    using Real = typename C::Real;
-    using G0 = Col0<N, DT>;
-    using Ff = TeamFFT<N, G0::T, Real, -1, false>;
-    using Fi = TeamFFT<N, G0::T, Real, +1, true>;
-    using WI = W2Index<N, Cfg<N, DT>::BS, PairW2<N, DT>::value || LaneW2<N, DT>::value>;
-    extern __shared__ __align__(16) unsigned char smem[];
-
-    if (int(blockIdx.x) >= bt.count * G0::groups) return;
-    const Prob<DT>& P = bt.p[blockIdx.x / G0::groups];
-    const auto& w2 = P.w2;
-    const typename C::Kt* __restrict__ K = P.K;
-    const typename C::Kt* __restrict__ Kb = P.Kb;
-    const cx<Real>* __restrict__ tw = P.tw;
-    const int g = threadIdx.x / (2 * G0::T);  // row pair within the workgroup
-    const int set = threadIdx.x & 1;
-    const int t = (threadIdx.x >> 1) % G0::T;
-    const int qg = (blockIdx.x % G0::groups) * G0::G + g;
-    const bool live = qg < N;  // the last workgroup may hold pairs past the end
-    const int q = live ? qg : N - 1;
-    cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem) + size_t(g) * 2 * N;
-    const int k1 = set == 0 ? q : (q == 0 ? N : 2 * N - q);
-    const int kt1 = (q == 0) ? (set ? N : 0) : q;
-    const int partner = (q == 0) ? set : 1 - set;
-    const typename C::Kt* Krow = K + psn_host::k_index(N, kt1, 0, 0);  // column 0 of plane kt1
-    const typename C::Kt* Kbr = Kb + size_t(kt1) * (N + 1);
-
-    static_assert(Ff::EM == Fi::EM, "same plan, reversed");
-    cx<Real> x[Ff::EI], acc[Ff::EI];
-    Ff::each_in(t, [&](int e) { x[e] = w2.ld(WI::at(Ff::in_pos(t, e), k1, 0)); });
-    LdsCols<Real> lds{sb + set, 2, 0};
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        cx<Real> d[Ff::EM];
-        Ff::each_in(t, [&](int e) { d[e] = p ? x[e] * tw[Ff::in_pos(t, e)] : x[e]; });
-        Ff::run(d, t, tw, lds);
-        __syncthreads();
-        Ff::each_out(t, [&](int e) { sb[set * N + Ff::out_pos(t, e)] = d[e]; });
-        __syncthreads();
-        Ff::each_out(t, [&](int e) {
-            const int m = Ff::out_pos(t, e);
-            const int k0 = 2 * m + p;
-            const int kt0 = k0 <= N ? k0 : 2 * N - k0;
-            const int mp = p == 0 ? (m == 0 ? 0 : N - m) : N - 1 - m;
-            const cx<Real> zp = conj(sb[partner * N + mp]);
-            d[e] = scale(d[e], Real(Krow[size_t(kt0) * psn_host::k_tile(N)])) + scale(zp, Real(Kbr[kt0]));
-        });
-        Fi::run(d, t, tw, lds);
-        Fi::each_out(t, [&](int e) {
-            if (p == 0) acc[e] = d[e];
-            else acc[e] = acc[e] + mul_conj(d[e], tw[Fi::out_pos(t, e)]);
-        });
-    }
-    if (live) {
-        Fi::each_out(t, [&](int e) { w2.st(WI::at(Fi::out_pos(t, e), k1, 0), acc[e]); });
     }
 }
 
@@ -770,24 +816,9 @@ p2p_fwd(const Batch<DT> bt) {
 // S for the odd ones); then u[2i] = P[i] + w^-2i R[i] and
 // u[2i+1] = Q[i] + w^-(2i+1) S[i].  Each lane loads and stores the pair
 // (x[2i], x[2i+1]) of its column as one access; all four chains advance in
-// lockstep, G of them per LDS exchange round.  Column 0 is left to p3_col0.
-// Per-stage twiddle rows for the half-length transforms of the paired middle
-// pass (n >= 512, where the saved index arithmetic outweighs the fill).
-template <int N>
-struct P3PRows {
-    static constexpr bool value = N >= 512;
-};
-template <int N, int DT, int TT>
-constexpr size_t p3p_tw_entries() {
-    using Real = typename Cfg<N, DT>::Real;
-    using Ff = TeamFFT<N / 2, TT, Real, -1, false>;
-    using Fi = TeamFFT<N / 2, TT, Real, +1, true>;
-    if constexpr (P3PRows<N>::value) return Ff::rows_size() + (Ff::template same_rows<Fi>() ? 0 : Fi::rows_size());
-    else return TwLds<Real>::slots(N);
-}
-
+// lockstep, G of them per LDS exchange round.  Column 0 is col0_conv's.
 template <int N, int DT, int B, int TT, int SL, int G>
-__global__ void __launch_bounds__((B * TT * SL), (G < 4 && DT == DT_F32 ? 2 : 1))
+__global__ void __launch_bounds__((B * TT * SL), (TeamFFT<N / 2, TT, typename Prec<DT>::Real, -1, false>::EM <= 8 ? 4 : 2))
 p3p_conv(const Batch<DT> bt) {
     using C = Cfg<N, DT>;
     using Real = typename C::Real;
@@ -805,7 +836,10 @@ p3p_conv(const Batch<DT> bt) {
     cx<Real>* sb = reinterpret_cast<cx<Real>*>(smem);
     cx<Real>* stw = sb + size_t(G) * H * B * SL;
 
-    const int ug = xcd_unit();
+    constexpr size_t lds_bytes = lds_p3p<N, DT, B, TT, SL, G>();
+    const int first = Col0<N, DT, B * TT * SL, lds_bytes>::blocks(bt.count);
+    if (int(blockIdx.x) < first) return col0_conv<N, DT, B * TT * SL, lds_bytes>(bt, int(blockIdx.x), smem);
+    const int ug = xcd_unit(first);
     if (ug >= bt.count * units) return;  // whole workgroup
     const Prob<DT>& P = bt.p[ug / units];
     const auto& w2 = P.w2;
@@ -830,7 +864,8 @@ p3p_conv(const Batch<DT> bt) {
                   "lane byte offsets fit 32 bits");
     // pair i = in_pos(t, e) of row q (set 0) or M-q (set 1, 2 BS elements on)
     const size_t ub = WI::at(0, q, tile * B);
-    const uint32_t xl = uint32_t(2 * c) + uint32_t(set) * (2 * C::BS) + uint32_t(t) * uint32_t(sp);
+    // (the lanes of column 0, which col0_conv has, take column 1's and store nothing)
+    const uint32_t xl = uint32_t(2 * (k2 == 0 ? 1 : c)) + uint32_t(set) * (2 * C::BS) + uint32_t(t) * uint32_t(sp);
     auto xb = [&](int e) { return ub + size_t(Ff::in_pos(0, e)) * sp; };
 
     static_assert(Ff::EM == Fi::EM, "same plan, reversed");
@@ -966,7 +1001,7 @@ p4p_inv(const Batch<DT> bt) {
 //   1  line i0 along i1: DFT_n(x w^(p i1)), written to row m, column i0
 //   2  row m along i0: both parities of k0, x K, inverse, back to row m
 //      (k2 = 0, the packed column: Z' = a Z(k) + b conj(Z(-k)), the partner row
-//      and position read from LDS, as in p3_col0)
+//      and position read from LDS, as in col0_conv)
 //   3  line i0 along m: inverse, times w^-(p i1)
 // A row's own LDS is the exchange area of the team that has it; the row pitch
 // of 8 mod 16 spreads a column's accesses over the banks.
@@ -1146,10 +1181,10 @@ inline bool allow_lds(const void* fn, size_t bytes) {
 //     third: 8 elements on a power-of-two team, on N / 8 threads, together, and
 //     all odd factors in every thread (12 or 20 elements).
 //   P3: one row with the chains one after the other; the row pair k1, M-k1; the
-//     chains together (odd factor: 12 or 20 elements, the row pair, which is the
-//     fastest for many densities per launch: 13 of 160^3 FP32 0.51 against
-//     0.54 ms, while one density takes 67 against 51 us); four elements (odd
-//     factor: 8 on N / 8 threads).
+//     chains together (FP32 with an odd factor: 12 or 20 elements, the row pair,
+//     which is the fastest for many densities per launch: 13 of 160^3 0.51 against
+//     0.54 ms, while one density takes 67 against 51 us); with an odd factor, 8
+//     elements on N / 8 threads.
 // The one-chain exchange stages the W2 runs of P2 in two rounds of n slots.
 struct TileV {
     int B, TT;
@@ -1170,7 +1205,7 @@ constexpr bool tile_ok(int N, TileV v, int cxbytes, int ip, bool axis0) {
 template <int N, int DT>
 struct Sched {
     using C = Cfg<N, DT>;
-    static constexpr TileV d24{C::BS, C::T24, 1, mid_plan(N) || C::IP == 2}, d3{C::BP3, C::T3, 1, true};
+    static constexpr TileV d24{C::BS, C::T24, 1, mid_plan(N) || C::IP == 2}, d3{C::BP3, C::T3, N % 4 ? 2 : 1, true};  // 162: the row pair, whose 108 threads hold column 0's teams
     static constexpr int odd = odd_part(N);
     static constexpr bool mid = mid_plan(N);
     static constexpr int e16 = odd > 1 ? odd * 2 : elems_per_thread(N, 4), eo = odd * 4;
@@ -1182,8 +1217,8 @@ struct Sched {
         pick24(TileV{C::BS, C::T24, 1, !d24.SEQ}),
         pick24(mid ? TileV{C::BS, N / eo, 1, true} : TileV{C::BS, N / (odd > 1 ? eo : 4)})};
     static constexpr TileV v3[psn_host::kScheduleCandidates] = {
-        d3, pick3(TileV{C::BP3, C::T3, 2, true}), pick3(mid ? TileV{C::BP3, N / eo, 2, true} : TileV{C::BP3, C::T3}),
-        pick3(mid ? TileV{C::BP3, tm, 1, true} : TileV{C::BP3, N / (odd > 1 ? odd * 2 : 4), 1, true})};
+        d3, pick3(TileV{C::BP3, C::T3, 2, true}), pick3(mid && DT == DT_F32 ? TileV{C::BP3, N / eo, 2, true} : TileV{C::BP3, C::T3, d3.SL}),
+        mid && N % 4 == 0 ? pick3(TileV{C::BP3, tm, 1, true}) : d3};
     static_assert(tile_ok(N, d24, C::CX, C::IP, false) && tile_ok(N, d3, C::CX, C::IP, true), "default tiles must fit");
 };
 
@@ -1231,15 +1266,6 @@ template <int N, int DT, int B, int TT, bool SEQ>
 constexpr size_t lds_p24() {
     return (size_t(SEQ ? 1 : 2) * Cfg<N, DT>::IP * B * N + TwLds<typename Cfg<N, DT>::Real>::slots(N)) * Cfg<N, DT>::CX;
 }
-template <int N, int DT, int B, int TT, int SL, bool SEQ>
-constexpr size_t lds_p3() {
-    using Real = typename Cfg<N, DT>::Real;
-    using Ff = TeamFFT<N, TT, Real, -1, false>;
-    using Fi = TeamFFT<N, TT, Real, +1, true>;
-    const size_t rows = P3Rows<N>::value ? Ff::rows_size() + (Ff::template same_rows<Fi>() ? 0 : Fi::rows_size())
-                                         : TwLds<Real>::slots(N);
-    return (size_t(SEQ ? 1 : 2) * B * SL * N + rows) * Cfg<N, DT>::CX;
-}
 
 template <int N, int DT, int I>
 hipError_t launch_p2(const Batch<DT>& bt, hipStream_t s) {
@@ -1266,12 +1292,13 @@ hipError_t launch_p4(const Batch<DT>& bt, hipStream_t s) {
 template <int N, int DT, int I>
 hipError_t launch_p3(const Batch<DT>& bt, hipStream_t s) {
     constexpr TileV v = Sched<N, DT>::v3[I];
-    const size_t lds = lds_p3<N, DT, v.B, v.TT, v.SL, v.SEQ>();
+    constexpr size_t lds = lds_p3<N, DT, v.B, v.TT, v.SL, v.SEQ>();
+    using G0 = Col0<N, DT, v.B * v.TT * v.SL, lds>;
     static const bool ok = allow_lds(reinterpret_cast<const void*>(&p3_conv<N, DT, v.B, v.TT, v.SL, v.SEQ>), lds);
     if (!ok) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((p3_conv<N, DT, v.B, v.TT, v.SL, v.SEQ>),
-                       dim3(xcd_grid(long(bt.count) * (2 / v.SL) * N * (N / v.B))), dim3(v.B * v.TT * v.SL), lds, s,
-                       bt);
+                       dim3(G0::blocks(bt.count) + xcd_grid(long(bt.count) * (2 / v.SL) * N * (N / v.B))),
+                       dim3(v.B * v.TT * v.SL), lds, s, bt);
     return hipSuccess;
 }
 
@@ -1302,13 +1329,14 @@ template <int N, int DT, int I>
 hipError_t launch_p3p(const Batch<DT>& bt, hipStream_t s) {
     constexpr TileP v = SchedP<N, DT>::v3[I];
     static_assert(tilep_ok(N, v, Cfg<N, DT>::CX), "paired axis-0 tile must fit");
-    const size_t lds = (size_t(v.G) * (N / 2) * v.B * v.SL + p3p_tw_entries<N, DT, v.TT>()) * Cfg<N, DT>::CX;
+    constexpr size_t lds = lds_p3p<N, DT, v.B, v.TT, v.SL, v.G>();
+    using G0 = Col0<N, DT, v.B * v.TT * v.SL, lds>;
     static const bool ok =
         allow_lds(reinterpret_cast<const void*>(&p3p_conv<N, DT, v.B, v.TT, v.SL, v.G>), lds);
     if (!ok) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((p3p_conv<N, DT, v.B, v.TT, v.SL, v.G>),
-                       dim3(xcd_grid(long(bt.count) * (2 / v.SL) * N * (N / v.B))), dim3(v.B * v.TT * v.SL), lds,
-                       s, bt);
+                       dim3(G0::blocks(bt.count) + xcd_grid(long(bt.count) * (2 / v.SL) * N * (N / v.B))),
+                       dim3(v.B * v.TT * v.SL), lds, s, bt);
     return hipSuccess;
 }
 
@@ -1350,7 +1378,7 @@ hipError_t launch_p3v(const Batch<DT>& bt, hipStream_t s, int v) {
     }
 }
 
-// Enqueue the kernels of one solve (six; three for PlaneCfg sizes) for bt.count
+// Enqueue the kernels of one solve (five; three for PlaneCfg sizes) for bt.count
 // problems of size N with schedule (v24 for P2/P4, v3 for P3).
 template <int N, int DT>
 hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, int v3) {
@@ -1380,8 +1408,6 @@ hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, 
         if ((e = launch_p24<N, DT>(bt, s, v24, true)) != hipSuccess) return e;
         mark(2);
         if ((e = launch_p3v<N, DT>(bt, s, v3)) != hipSuccess) return e;
-        using G0 = Col0<N, DT>;
-        hipLaunchKernelGGL((p3_col0<N, DT>), dim3(cnt * G0::groups), dim3(2 * G0::T * G0::G), G0::lds, s, bt);
         mark(3);
         if ((e = launch_p24<N, DT>(bt, s, v24, false)) != hipSuccess) return e;
         mark(4);
