@@ -203,7 +203,9 @@ __global__ void k_correction(const double* __restrict__ tau, const double* __res
 }
 
 // K(k0, k1, n) for every (k0, k1), FP64: the k2 = n column, which the
-// octant stores folded with k2 = 0.  Kn[k1 (n + 1) + k0].
+// octant stores folded with k2 = 0.  Kn[k1 (n + 1) + k0].  Few threads, so bound
+// by the latency of the loads: those of sixteen terms in flight, added in order
+// (n = 128 64 -> 30 us, n = 512 70 -> 43).
 __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__ A1, const double* __restrict__ A2,
                        const double* __restrict__ w, int terms, int n, double p0, double p1, double p2,
                        const double* __restrict__ Cc, bool fourier, double* __restrict__ Kn) {
@@ -211,6 +213,7 @@ __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__
     if (k0 > n) return;
     const int np1 = n + 1;
     double s = 0.0;
+#pragma unroll 16
     for (int j = 0; j < terms; ++j)
         s = fma(A0[size_t(j) * np1 + k0] * A1[size_t(j) * np1 + k1], w[j] * A2[size_t(j) * np1 + n], s);
     const double b0 = 2.0 * kPi * k0 / p0, b1 = 2.0 * kPi * k1 / p1, b2 = 2.0 * kPi * n / p2;
@@ -219,16 +222,18 @@ __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__
 }
 
 // Octant assembly, k2 = 0..n-1: a workgroup of 256 threads computes a tile of
-// 128 k0 x 64 k2 of one k1 plane, each thread 4 k0 x 8 k2 (k0 = k0b + r +
-// 32 i, k2 = k2b + q + 8 c with q = tid % 8, r = tid / 8), so that the eight
-// lanes of a k0 row write 8 consecutive k2 of the tiled octant.  The terms
-// stream through LDS in chunks of 16: a_j(k0) and w_j a_j(k2).  With SYM
-// (A0 == A1) only tiles with k0b <= k1 run and entries with k0 <= k1 are
-// written, to (k0, k1) and (k1, k0).
+// 128 k0 x 64 k2 of one k1 plane.  The terms stream through LDS in chunks of 32:
+// a_j(k0) and w_j a_j(k2).  With SYM (A0 == A1) only tiles with k0b <= k1 run,
+// waves whose rows all lie past k1 leave the products out, and entries with
+// k0 <= k1 are written, to (k0, k1) and (k1, k0).
+// The loads of a chunk are made all at once, from clamped addresses, while the
+// chunk before is multiplied: loads under one branch each wait for one another,
+// 12 us a chunk.  n = 128 FP32 95 -> 67 us, n = 162 FP64 100 -> 84, n = 512 FP32 1305
+// -> 1035 (every value as before).
 constexpr int kTile0 = 128, kTile2 = 64, kChunk = 32;
 
 template <class Kt, bool SYM>
-__global__ void __launch_bounds__(256) k_gemm(const double* __restrict__ A0, const double* __restrict__ A1,
+__global__ void __launch_bounds__(256, 3) k_gemm(const double* __restrict__ A0, const double* __restrict__ A1,
                                               const double* __restrict__ A2, const double* __restrict__ w, int terms,
                                               int n, double p0, double p1, double p2,
                                               const double* __restrict__ Cc, bool fourier,
@@ -248,18 +253,41 @@ __global__ void __launch_bounds__(256) k_gemm(const double* __restrict__ A0, con
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[i][c] = psn_d4{0.0, 0.0, 0.0, 0.0};
+    // this thread's part of a chunk: column ca of a_j(k0), column cb of w_j a_j(k2)
+    constexpr int ra = kChunk * kTile0 / 256, rb = kChunk * kTile2 / 256;
+    // (its rows the same for the whole wave)
+    const int ca = tid % kTile0, ja = __builtin_amdgcn_readfirstlane(tid / kTile0);
+    const int cb = tid % kTile2, jb = __builtin_amdgcn_readfirstlane(tid / kTile2);
+    const bool ina = k0b + ca <= n, inb = k2b + cb < n;
+    const int oa = ina ? k0b + ca : n, ob = inb ? k2b + cb : n;
+    const bool busy = !SYM || k0b + 32 * wv <= k1;
+    double va[ra], vb[rb], v1;
+    auto fetch = [&](int j0) {
+#pragma unroll
+        for (int i = 0; i < ra; ++i)
+            va[i] = (A0 + size_t(min(j0 + ja + i * (256 / kTile0), terms - 1)) * np1)[oa];
+#pragma unroll
+        for (int i = 0; i < rb; ++i)
+            vb[i] = (A2 + size_t(min(j0 + jb + i * (256 / kTile2), terms - 1)) * np1)[ob];
+        v1 = A1[size_t(min(j0 + tid % kChunk, terms - 1)) * np1 + k1];
+    };
+    fetch(0);
     for (int j0 = 0; j0 < terms; j0 += kChunk) {
         __syncthreads();  // the previous chunk's reads are done
-        for (int idx = tid; idx < kChunk * kTile0; idx += 256) {
-            const int jj = idx / kTile0, c = idx % kTile0, j = j0 + jj, k0 = k0b + c;
-            sa[jj][c] = (j < terms && k0 <= n) ? A0[size_t(j) * np1 + k0] : 0.0;
+#pragma unroll
+        for (int i = 0; i < ra; ++i) {
+            const int jj = ja + i * (256 / kTile0);
+            sa[jj][ca] = ina && j0 + jj < terms ? va[i] : 0.0;
         }
-        for (int idx = tid; idx < kChunk * kTile2; idx += 256) {
-            const int jj = idx / kTile2, c = idx % kTile2, j = j0 + jj, k2 = k2b + c;
-            sb[jj][c] = (j < terms && k2 < n) ? w[j] * A2[size_t(j) * np1 + k2] : 0.0;
+#pragma unroll
+        for (int i = 0; i < rb; ++i) {
+            const int jj = jb + i * (256 / kTile2);
+            sb[jj][cb] = inb && j0 + jj < terms ? w[min(j0 + jj, terms - 1)] * vb[i] : 0.0;
         }
-        if (tid < kChunk) s1[tid] = j0 + tid < terms ? A1[size_t(j0 + tid) * np1 + k1] : 0.0;
+        if (tid < kChunk) s1[tid] = j0 + tid < terms ? v1 : 0.0;
         __syncthreads();
+        if (j0 + kChunk < terms) fetch(j0 + kChunk);
+        if (!busy) continue;
         // four k-steps of four terms: lane (li, lg) gives term 4 s + lg of row
         // li (the product a_j(k0) a_j(k1)) and of column li (w_j a_j(k2))
 #pragma unroll
