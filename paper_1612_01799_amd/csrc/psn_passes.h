@@ -161,7 +161,7 @@ struct W1Index {
 };
 
 // Cubes whose axes 1 and 0 run plane by plane in one launch (plane_conv): three
-// launches a solve instead of six, up to n = 64.  One FP32 density: n = 32
+// launches a solve instead of five (and one for column 0), up to n = 64.  One FP32 density: n = 32
 // 26 -> 15.5 us, n = 48 29 -> 19.5, n = 64 34 -> 23; FP64 35 -> 21 at n = 48,
 // 39 -> 30 at n = 64; 13 densities a launch 95 -> 85 us (n = 64 FP32).  At n = 96
 // FP32 one density still gains (57 -> 52 us), but a CU holds one workgroup of a
