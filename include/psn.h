@@ -234,9 +234,9 @@ psn_status psn_plan_gs_table(const psn_plan *p, double *tau, double *w, int cap,
 /* Copy the built kernel spectrum to a host array octant[(n0+1)(n1+1)(n2+1)]
  * ((n+1)^3 on a grid of n points per axis), FP64, index [k0][k1][k2] with
  * k_q = 0..n_q the folded frequency index, in the paper's normalisation (no
- * 1/(8 n0 n1 n2) factor).  With PSN_CORRECTION_FOURIER: the G-tensor alone.
- * Synchronous.
- * Errors: PSN_EINVAL, PSN_ESTATE, PSN_EDEVICE. */
+ * 1/(8 n0 n1 n2) factor).  With PSN_CORRECTION_FOURIER: the G-tensor alone,
+ * built again into device memory of this call's own.  Synchronous.
+ * Errors: PSN_EINVAL, PSN_ESTATE, PSN_EDEVICE, PSN_ENOMEM. */
 psn_status psn_kernel_download(const psn_plan *p, double *octant);
 
 /* Release the plan and its device memory.  NULL is a no-op. */

@@ -85,9 +85,11 @@ __host__ __device__ constexpr size_t g_k_index(int n0, int n2, int k0, int k1, i
 // all three k are even, and 0 elsewhere, makes the padded convolution add
 // exactly the term that a separate n-point transform pair would: the solve
 // costs the same in both modes (n = 512 FP32: 4.16 -> 2.99 ms, the five passes
-// over the density's half spectrum gone).
-__host__ __device__ constexpr double correction_weight(bool fourier, int k0, int k1, int k2) {
-    return fourier ? (((k0 | k1 | k2) & 1) ? 0.0 : 8.0) : 1.0;
+// over the density's half spectrum gone).  kCorrectionNone: the G-tensor alone.
+constexpr int kCorrectionNone = 2;  // beside the values of psn_correction
+__host__ __device__ constexpr double correction_weight(int mode, int k0, int k1, int k2) {
+    return mode == PSN_CORRECTION_FOLDED ? 1.0
+           : mode == PSN_CORRECTION_FOURIER && ((k0 | k1 | k2) & 1) == 0 ? 8.0 : 0.0;
 }
 
 // k1 block of the W2 layout: the largest power of two <= sqrt(2n) dividing 2n
@@ -141,14 +143,15 @@ hipError_t tune_f32(const psn_plan* p, hipStream_t stream, int* best24, int* bes
 hipError_t tune_split(const psn_plan* p, hipStream_t stream, int* best24, int* best3);
 constexpr int kScheduleCandidates = 4;
 
-// Kernel spectrum build on the device (FP64), written into p->K / p->Kb in
-// the plan's storage type, plus C0/C2 into the two doubles at d_c.
+// Kernel spectrum build on the device (FP64), with the correction entering by
+// `mode` (correction_weight), written into K / Kb in the plan's storage type,
+// plus C0/C2 into the two doubles at d_c.
 // d_A is scratch of kbuild_scratch_doubles(n, terms) doubles: three mode
 // tables of terms x (n+1), three moment tables, and the k2 = n column.
 size_t kbuild_scratch_doubles(int n, int terms);
-hipError_t launch_kernel_build(psn_plan* p, const double* d_tau, const double* d_w, int terms,
-                               const double* d_glx, const double* d_glw, double* d_A, double* d_c,
-                               hipStream_t stream);
+hipError_t launch_kernel_build(const psn_plan* p, int mode, void* K, void* Kb, const double* d_tau,
+                               const double* d_w, int terms, const double* d_glx, const double* d_glw, double* d_A,
+                               double* d_c, hipStream_t stream);
 
 size_t elem_bytes(psn_dtype dt);        // bytes of one complex value in the compute precision (8 or 16)
 size_t w1_bytes(psn_dtype dt);          // bytes of one complex element of W1 (8, 16, or 12 split)

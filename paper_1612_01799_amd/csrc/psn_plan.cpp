@@ -250,6 +250,34 @@ void free_device(psn_plan* p) {
     p->built = false;
 }
 
+// The kernel spectrum of p's geometry in its storage type, with the correction
+// entering by `mode`, into K and Kb, and C0, C2 into cc.  Synchronises s.
+psn_status build_spectrum(const psn_plan* p, int mode, void* K, void* Kb, double* cc, hipStream_t s) {
+    double gl[32];
+    gauss_legendre16(gl, gl + 16);
+    const int terms = (int)p->tau.size();
+    const int nmax = std::max(p->ng[0], std::max(p->ng[1], p->ng[2]));
+    DevBuf d_tau, d_w, d_gl, d_A, d_c;
+    size_t tot = 0;
+    psn_status st = PSN_OK;
+    if ((st = dev_alloc(&d_tau.p, terms * 8, &tot)) || (st = dev_alloc(&d_w.p, terms * 8, &tot)) ||
+        (st = dev_alloc(&d_gl.p, sizeof gl, &tot)) ||
+        (st = dev_alloc(&d_A.p, psn_host::kbuild_scratch_doubles(nmax, terms) * 8, &tot)) ||
+        (st = dev_alloc(&d_c.p, 2 * 8, &tot)))
+        return st;
+    double* const dgl = static_cast<double*>(d_gl.p);
+    bool ok = hip_ok(hipMemcpyAsync(d_tau.p, p->tau.data(), terms * 8, hipMemcpyHostToDevice, s), "copy tau") &&
+              hip_ok(hipMemcpyAsync(d_w.p, p->w.data(), terms * 8, hipMemcpyHostToDevice, s), "copy w") &&
+              hip_ok(hipMemcpyAsync(d_gl.p, gl, sizeof gl, hipMemcpyHostToDevice, s), "copy nodes");
+    ok = ok && hip_ok(psn_host::launch_kernel_build(p, mode, K, Kb, static_cast<double*>(d_tau.p),
+                                                    static_cast<double*>(d_w.p), terms, dgl, dgl + 16,
+                                                    static_cast<double*>(d_A.p), static_cast<double*>(d_c.p), s),
+                      "kernel-spectrum launch");
+    ok = ok && hip_ok(hipMemcpyAsync(cc, d_c.p, 2 * sizeof(double), hipMemcpyDeviceToHost, s), "copy C0/C2");
+    ok = hip_ok(hipStreamSynchronize(s), "hipStreamSynchronize") && ok;  // also before gl and the buffers go
+    return ok ? PSN_OK : PSN_EDEVICE;
+}
+
 bool is_real_dtype(int d) { return d == PSN_F64 || d == PSN_F32 || d == PSN_SPLIT; }
 
 // Autotuned schedules, once per (n, precision) and process.  PSN_TUNE=0 keeps
@@ -595,38 +623,15 @@ psn_status psn_kernel_build(psn_plan* p, void* stream) {
         twf.assign(twd.begin(), twd.end());
         twsrc = twf.data();
     }
-    double glx[16], glw[16];
-    gauss_legendre16(glx, glw);
-    const int terms = (int)p->tau.size();
-
-    DevBuf d_tau, d_w, d_gl, d_A, d_c;
-    if ((st = dev_alloc(&d_tau.p, terms * 8, &tot)) || (st = dev_alloc(&d_w.p, terms * 8, &tot)) ||
-        (st = dev_alloc(&d_gl.p, 32 * 8, &tot)) || (st = dev_alloc(&d_A.p,
-                                  psn_host::kbuild_scratch_doubles(std::max(p->ng[0], std::max(p->ng[1], p->ng[2])),
-                                                                   terms) * 8,
-                                  &tot)) ||
-        (st = dev_alloc(&d_c.p, 2 * 8, &tot))) {
+    double cc[2] = {0, 0};
+    if (!hip_ok(hipMemcpyAsync(p->tw, twsrc, tw_entries * cxb, hipMemcpyHostToDevice, s), "copy twiddles"))
+        st = PSN_EDEVICE;
+    else
+        st = build_spectrum(p, p->correction, p->K, p->Kb, cc, s);
+    if (st) {
+        (void)hipStreamSynchronize(s);  // the twiddle copy has left its host buffer
         free_device(p);
         return st;
-    }
-    std::vector<double> gl(32);
-    std::memcpy(gl.data(), glx, sizeof glx);
-    std::memcpy(gl.data() + 16, glw, sizeof glw);
-    double cc[2] = {0, 0};
-    bool ok = hip_ok(hipMemcpyAsync(p->tw, twsrc, tw_entries * cxb, hipMemcpyHostToDevice, s), "copy twiddles") &&
-              hip_ok(hipMemcpyAsync(d_tau.p, p->tau.data(), terms * 8, hipMemcpyHostToDevice, s), "copy tau") &&
-              hip_ok(hipMemcpyAsync(d_w.p, p->w.data(), terms * 8, hipMemcpyHostToDevice, s), "copy w") &&
-              hip_ok(hipMemcpyAsync(d_gl.p, gl.data(), 32 * 8, hipMemcpyHostToDevice, s), "copy nodes");
-    ok = ok && hip_ok(psn_host::launch_kernel_build(p, static_cast<double*>(d_tau.p), static_cast<double*>(d_w.p),
-                                                    terms, static_cast<double*>(d_gl.p),
-                                                    static_cast<double*>(d_gl.p) + 16, static_cast<double*>(d_A.p),
-                                                    static_cast<double*>(d_c.p), s),
-                      "kernel-spectrum launch");
-    ok = ok && hip_ok(hipMemcpyAsync(cc, d_c.p, sizeof cc, hipMemcpyDeviceToHost, s), "copy C0/C2");
-    ok = ok && hip_ok(hipStreamSynchronize(s), "hipStreamSynchronize");
-    if (!ok) {
-        free_device(p);
-        return PSN_EDEVICE;
     }
     p->C0 = cc[0];
     p->C2 = cc[1];
@@ -1004,21 +1009,33 @@ psn_status psn_kernel_download(const psn_plan* p, double* octant) {
     const size_t n = p->n, np1 = n + 1;
     const size_t kb = psn_host::kernel_elem_bytes(p->dtype);
     std::vector<unsigned char> hk(np1 * np1 * n * kb), hb(np1 * np1 * kb);
-    if (!hip_ok(hipMemcpy(hk.data(), p->K, hk.size(), hipMemcpyDeviceToHost), "copy K") ||
-        !hip_ok(hipMemcpy(hb.data(), p->Kb, hb.size(), hipMemcpyDeviceToHost), "copy Kb"))
+    const void *K = p->K, *Kb = p->Kb;
+    DevBuf gk, gb;
+    if (p->correction == PSN_CORRECTION_FOURIER) {
+        // the octant is the G-tensor alone, built again without the symbol: taking
+        // the symbol off the stored sum would leave its rounding behind
+        (void)hipGetLastError();
+        size_t tot = 0;
+        double cc[2];
+        int dev = -1;
+        if (!hip_ok(hipGetDevice(&dev), "hipGetDevice") || !hip_ok(hipSetDevice(p->device), "hipSetDevice"))
+            return PSN_EDEVICE;
+        psn_status st = PSN_OK;
+        if (!(st = dev_alloc(&gk.p, hk.size(), &tot)) && !(st = dev_alloc(&gb.p, hb.size(), &tot)))
+            st = build_spectrum(p, psn_host::kCorrectionNone, gk.p, gb.p, cc, nullptr);
+        if (!hip_ok(hipSetDevice(dev), "hipSetDevice") && !st) st = PSN_EDEVICE;
+        if (st) return st;
+        K = gk.p;
+        Kb = gb.p;
+    }
+    if (!hip_ok(hipMemcpy(hk.data(), K, hk.size(), hipMemcpyDeviceToHost), "copy K") ||
+        !hip_ok(hipMemcpy(hb.data(), Kb, hb.size(), hipMemcpyDeviceToHost), "copy Kb"))
         return PSN_EDEVICE;
     auto get = [&](const std::vector<unsigned char>& v, size_t i) -> double {
         if (kb == 4) return (double)reinterpret_cast<const float*>(v.data())[i];
         return reinterpret_cast<const double*>(v.data())[i];
     };
     const double M = 2.0 * n, inv = M * M * M;
-    // with the correction by the Fourier series the octant is the G-tensor
-    // alone: the symbol that K also holds is taken off again
-    const bool fourier = p->correction == PSN_CORRECTION_FOURIER;
-    auto kap2 = [&](int q, size_t k) {
-        const double v = 2.0 * kPi * double(k) / p->period[q];
-        return v * v;
-    };
     for (size_t a = 0; a < np1; ++a)
         for (size_t b = 0; b < np1; ++b) {
             double* dst = octant + (a * np1 + b) * np1;
@@ -1026,10 +1043,6 @@ psn_status psn_kernel_download(const psn_plan* p, double* octant) {
             dst[0] = (al + be) * inv;
             dst[n] = (al - be) * inv;
             for (size_t c = 1; c < n; ++c) dst[c] = get(hk, psn_host::k_index(int(n), int(b), int(a), int(c))) * inv;
-            if (!fourier) continue;
-            for (size_t c = 0; c <= n; ++c)
-                dst[c] -= psn_host::correction_weight(true, int(a), int(b), int(c)) *
-                          (p->C0 - (p->C2 / 6.0) * (kap2(0, a) + kap2(1, b) + kap2(2, c)));
         }
     return PSN_OK;
 }
