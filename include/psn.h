@@ -142,7 +142,8 @@ psn_status psn_plan_create_grid(const int *n, const double *a, const double *b, 
  * With PSN_TUNE_CACHE naming a file, a schedule recorded there for the same
  * (n, precision) is taken without timing, and a newly timed one is appended,
  * so that separate processes pick the same candidates (candidates agree only
- * within rounding, see psn_plan_set_schedule).
+ * within rounding, see psn_plan_set_schedule).  Records carry a tag of the
+ * candidates they name; those of a library with other candidates are ignored.
  * Synchronises `stream` before returning.  Idempotent.
  * Errors: PSN_EINVAL, PSN_ENOMEM, PSN_EDEVICE. */
 psn_status psn_kernel_build(psn_plan *p, void *stream);

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
+#include <cstdint>
 #include <vector>
 
 #include "../../include/psn.h"
@@ -142,6 +143,10 @@ hipError_t tune_f64(const psn_plan* p, hipStream_t stream, int* best24, int* bes
 hipError_t tune_f32(const psn_plan* p, hipStream_t stream, int* best24, int* best3);
 hipError_t tune_split(const psn_plan* p, hipStream_t stream, int* best24, int* best3);
 constexpr int kScheduleCandidates = 4;
+// what the candidate indices name in this build (0: a size without candidates)
+uint32_t sched_tag_f64(int n);
+uint32_t sched_tag_f32(int n);
+uint32_t sched_tag_split(int n);
 
 // Kernel spectrum build on the device (FP64), with the correction entering by
 // `mode` (correction_weight), written into K / Kb in the plan's storage type,

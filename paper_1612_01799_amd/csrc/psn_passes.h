@@ -1261,6 +1261,34 @@ struct SchedP {
                    C::CX, C::BS)};
 };
 
+// What the candidate indices of this size and precision name, in 32 bits (FNV-1a
+// over the tiles), for records that outlive the library: an index recorded by a
+// build with another table would name another tile.  0: one form, no candidates.
+template <int N, int DT>
+constexpr uint32_t sched_tag() {
+    if (PlaneCfg<N, DT>::value) return 0;
+    uint32_t h = 2166136261u;
+    auto add = [&](int v) { h = (h ^ uint32_t(v)) * 16777619u; };
+    auto tile = [&](const TileV& v) { add(v.B), add(v.TT), add(v.SL), add(v.SEQ); };
+    add(Cfg<N, DT>::IP);
+    for (const TileV& v : Sched<N, DT>::v24) tile(v);
+    if constexpr (PairW2<N, DT>::value)
+        for (const TileP& v : SchedP<N, DT>::v3) add(v.B), add(v.TT), add(v.SL), add(v.G);
+    else
+        for (const TileV& v : Sched<N, DT>::v3) tile(v);
+    return h ? h : 1;
+}
+template <int DT>
+uint32_t sched_tag_of(int n) {
+    switch (n) {
+#define PSN_CASE(NN) \
+    case NN: return sched_tag<NN, DT>();
+        PSN_FOR_EACH_SIZE(PSN_CASE)
+#undef PSN_CASE
+        default: return 0;
+    }
+}
+
 // LDS of the strided passes: the exchange area plus the stage twiddle rows
 template <int N, int DT, int B, int TT, bool SEQ>
 constexpr size_t lds_p24() {
@@ -1557,4 +1585,5 @@ hipError_t tune_plan(const psn_plan* p, hipStream_t s, int* best24, int* best3) 
     hipError_t tune_##SUFFIX(const psn_plan* p, hipStream_t stream, int* best24, int* best3) {                \
         return psn::tune_plan<DTV>(p, stream, best24, best3);                                                   \
     }                                                                                                           \
+    uint32_t sched_tag_##SUFFIX(int n) { return psn::sched_tag_of<DTV>(n); }                                    \
     }

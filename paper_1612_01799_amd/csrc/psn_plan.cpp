@@ -282,19 +282,32 @@ bool is_real_dtype(int d) { return d == PSN_F64 || d == PSN_F32 || d == PSN_SPLI
 
 // Autotuned schedules, once per (n, precision) and process.  PSN_TUNE=0 keeps
 // the default tiles.  PSN_TUNE_CACHE names a text file of lines
-// "n precision p24 p3": a recorded schedule is taken without timing and a
+// "n precision p24 p3 tag": a recorded schedule is taken without timing and a
 // newly timed one is appended, so separate processes agree on the candidates.
+// The tag (hexadecimal) identifies the table that the two indices name entries
+// of; a record of another table, or one without a tag, is timed anew.
+// (Untagged records of an earlier table were taken as they stood: at n = 512 FP64
+// index 2, the winner there, had become a tile of 1.67 + 1.38 ms for the axis-1
+// passes against 1.29 + 1.20.)  Sizes with one form of the passes have no tag.
 std::mutex g_tune_mutex;
 std::map<std::pair<int, int>, std::pair<int, int>> g_tuned;
+
+uint32_t sched_tag(int n, int dt) {
+    return dt == PSN_F64 ? psn_host::sched_tag_f64(n)
+           : dt == PSN_F32 ? psn_host::sched_tag_f32(n) : psn_host::sched_tag_split(n);
+}
 
 bool tune_cache_lookup(const char* path, int n, int dt, int* b24, int* b3) {
     FILE* f = std::fopen(path, "r");
     if (!f) return false;
-    int a, b, c, d;
+    const uint32_t want = sched_tag(n, dt);
+    char line[256];
     bool found = false;
-    while (std::fscanf(f, "%d %d %d %d", &a, &b, &c, &d) == 4) {
-        if (a == n && b == dt && c >= 0 && c < psn_host::kScheduleCandidates && d >= 0 &&
-            d < psn_host::kScheduleCandidates) {
+    while (std::fgets(line, sizeof line, f)) {
+        int a, b, c, d;
+        unsigned tag = 0;
+        if (std::sscanf(line, "%d %d %d %d %x", &a, &b, &c, &d, &tag) >= 4 && a == n && b == dt && tag == want &&
+            c >= 0 && c < psn_host::kScheduleCandidates && d >= 0 && d < psn_host::kScheduleCandidates) {
             *b24 = c;
             *b3 = d;
             found = true;  // the last record of a key wins
@@ -307,7 +320,9 @@ bool tune_cache_lookup(const char* path, int n, int dt, int* b24, int* b3) {
 void tune_cache_append(const char* path, int n, int dt, int b24, int b3) {
     FILE* f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "%d %d %d %d\n", n, dt, b24, b3);
+    std::fprintf(f, "%d %d %d %d", n, dt, b24, b3);
+    if (const uint32_t tag = sched_tag(n, dt)) std::fprintf(f, " %08x", tag);
+    std::fprintf(f, "\n");
     std::fclose(f);
 }
 
