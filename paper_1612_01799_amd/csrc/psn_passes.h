@@ -553,9 +553,16 @@ constexpr int p3_waves(int em, bool f32) {
     return em <= 9 ? 4 : em <= 12 ? 3 : 1;
 }
 
-template <int N, int DT, int B, int TT, int SL, bool SEQ>
+// EARLY (row pairs on teams of 12 elements per thread): the twiddles w stay in
+// registers and, in FP64, the kernel values are loaded with the data.  Fewer
+// waves fit, and many densities in one launch still run faster so: 32 of
+// n = 192, the 12-element teams late and early, FP32 2.07 and 1.96 ms; n = 96 FP32 288
+// and 238 us; the fastest late tile and this one, n = 192 FP64 3.90 and 3.73 ms,
+// n = 96 FP64 501 and 438 us.  20 elements early: 1.60 ms against 1.30 late (32 of 160, FP32).
+template <int N, int DT, int B, int TT, int SL, bool SEQ, bool EARLY>
 __global__ void __launch_bounds__((B * TT * SL),
-                                  (p3_waves(TeamFFT<N, TT, typename Prec<DT>::Real, -1, false>::EM, DT == DT_F32)))
+                                  (EARLY ? DT == DT_F32 ? 3 : 1
+                                         : p3_waves(TeamFFT<N, TT, typename Prec<DT>::Real, -1, false>::EM, DT == DT_F32)))
 p3_conv(const Batch<DT> bt) {
     using C = Cfg<N, DT>;
     using Real = typename C::Real;
@@ -633,10 +640,20 @@ p3_conv(const Batch<DT> bt) {
 
     static_assert(Ff::EM == Fi::EM, "same plan, reversed");
     cx<Real> d[2][Ff::EM];
+    cx<Real> w[EARLY ? Ff::EI : 1];
+    Real kk[2][Ff::EO];
+    auto load_k = [&]() {
+        Ff::each_out(t, [&](int e) {
+            kk[0][e] = kval(e, 0);
+            kk[1][e] = kval(e, 1);
+        });
+    };
     Ff::each_in(t, [&](int e) {
         d[0][e] = w2.ld(xb(e), xl);
-        d[1][e] = pre(e);
+        if constexpr (EARLY) d[1][e] = w[e] = gld(tw + Ff::in_pos(t, e));
+        else d[1][e] = pre(e);
     });
+    if constexpr (EARLY && DT != DT_F32) load_k();
     // Stage twiddles: per-stage rows of both transforms (shared when their
     // radices match) for n >= 512, where the saved index arithmetic outweighs
     // the scattered reads that fill them; else the swizzled 2N-entry table.
@@ -651,24 +668,23 @@ p3_conv(const Batch<DT> bt) {
     }
     Ff::each_in(t, [&](int e) { d[1][e] = d[0][e] * d[1][e]; });
     ChainLds<Real, SEQ> lds{sb, B * SL, c + B * set * (SL - 1)};
-    // Few values stay live across the transforms, so that more waves fit: the
-    // kernel values are loaded after the forward one, the twiddles w again at
-    // the end, and the addresses of the exchanges are formed anew for the
-    // inverse (here) instead of being kept.  n = 512 FP64: 166 -> 126 VGPRs,
+    // But for EARLY, few values stay live across the transforms, so that more
+    // waves fit: the kernel values are loaded after the forward one, the twiddles
+    // w again at the end, and the addresses of the exchanges are formed anew for
+    // the inverse (here) instead of being kept.  n = 512 FP64: 166 -> 126 VGPRs,
     // four waves per SIMD instead of three, 2.55 -> 2.39 ms; n = 320 FP64:
     // 212 -> 146, three instead of two.
     Ff::template run<2>(d, t, Tw{stw}, lds);
-    __builtin_amdgcn_sched_barrier(0);
-    Real kk[2][Ff::EO];
-    Ff::each_out(t, [&](int e) {
-        kk[0][e] = kval(e, 0);
-        kk[1][e] = kval(e, 1);
-    });
+    if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!EARLY || DT == DT_F32) load_k();
     // the multiply by K is folded into the first stage of the inverse
-    Fi::template run_scaled<2>(d, here(t), Tw{kRows ? rows_i : stw}, lds, kk);
-    __builtin_amdgcn_sched_barrier(0);
+    Fi::template run_scaled<2>(d, EARLY ? t : here(t), Tw{kRows ? rows_i : stw}, lds, kk);
+    if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);
     if (k2 != 0) {
-        Ff::each_in(t, [&](int e) { w2.st(xb(e), xl, twfma<+1>(d[1][e], pre(e), d[0][e])); });
+        Ff::each_in(t, [&](int e) {
+            if constexpr (EARLY) w2.st(xb(e), xl, twfma<+1>(d[1][e], w[e], d[0][e]));
+            else w2.st(xb(e), xl, twfma<+1>(d[1][e], pre(e), d[0][e]));
+        });
     }
 }
 
@@ -1190,6 +1206,7 @@ struct TileV {
     int B, TT;
     int SL = 1;        // rows per workgroup (the axis-0 pass only)
     bool SEQ = false;  // exchange the two chains one at a time (half the LDS)
+    bool EARLY = false;  // the axis-0 pass holds w and, in FP64, K from its start (p3_conv)
 };
 
 // ip: i0 per workgroup of the axis-1 passes; the axis-0 pass has SL rows per
@@ -1217,7 +1234,7 @@ struct Sched {
         pick24(TileV{C::BS, C::T24, 1, !d24.SEQ}),
         pick24(mid ? TileV{C::BS, N / eo, 1, true} : TileV{C::BS, N / (odd > 1 ? eo : 4)})};
     static constexpr TileV v3[psn_host::kScheduleCandidates] = {
-        d3, pick3(TileV{C::BP3, C::T3, 2, true}), pick3(mid && DT == DT_F32 ? TileV{C::BP3, N / eo, 2, true} : TileV{C::BP3, C::T3, d3.SL}),
+        d3, pick3(TileV{C::BP3, C::T3, 2, true}), pick3(mid && (DT == DT_F32 || odd == 3) ? TileV{C::BP3, N / eo, 2, true, odd == 3} : TileV{C::BP3, C::T3, d3.SL}),
         mid && N % 4 == 0 ? pick3(TileV{C::BP3, tm, 1, true}) : d3};
     static_assert(tile_ok(N, d24, C::CX, C::IP, false) && tile_ok(N, d3, C::CX, C::IP, true), "default tiles must fit");
 };
@@ -1269,7 +1286,7 @@ constexpr uint32_t sched_tag() {
     if (PlaneCfg<N, DT>::value) return 0;
     uint32_t h = 2166136261u;
     auto add = [&](int v) { h = (h ^ uint32_t(v)) * 16777619u; };
-    auto tile = [&](const TileV& v) { add(v.B), add(v.TT), add(v.SL), add(v.SEQ); };
+    auto tile = [&](const TileV& v) { add(v.B), add(v.TT), add(v.SL), add(v.SEQ), add(v.EARLY); };
     add(Cfg<N, DT>::IP);
     for (const TileV& v : Sched<N, DT>::v24) tile(v);
     if constexpr (PairW2<N, DT>::value)
@@ -1322,9 +1339,9 @@ hipError_t launch_p3(const Batch<DT>& bt, hipStream_t s) {
     constexpr TileV v = Sched<N, DT>::v3[I];
     constexpr size_t lds = lds_p3<N, DT, v.B, v.TT, v.SL, v.SEQ>();
     using G0 = Col0<N, DT, v.B * v.TT * v.SL, lds>;
-    static const bool ok = allow_lds(reinterpret_cast<const void*>(&p3_conv<N, DT, v.B, v.TT, v.SL, v.SEQ>), lds);
+    static const bool ok = allow_lds(reinterpret_cast<const void*>(&p3_conv<N, DT, v.B, v.TT, v.SL, v.SEQ, v.EARLY>), lds);
     if (!ok) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((p3_conv<N, DT, v.B, v.TT, v.SL, v.SEQ>),
+    hipLaunchKernelGGL((p3_conv<N, DT, v.B, v.TT, v.SL, v.SEQ, v.EARLY>),
                        dim3(G0::blocks(bt.count) + xcd_grid(long(bt.count) * (2 / v.SL) * N * (N / v.B))),
                        dim3(v.B * v.TT * v.SL), lds, s, bt);
     return hipSuccess;
