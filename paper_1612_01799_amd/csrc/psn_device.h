@@ -348,19 +348,28 @@ constexpr RadixPlan team_plan(int N, int E) {
     return mid == 2 || mid == 3 || mid == 5 || mid == 6 ? RadixPlan{3, {first, mid, last}} : RadixPlan{-1, {}};
 }
 
-// Elements per thread for a length-N line of the contiguous passes: a power of
-// two takes up to 16 (8 for 8-byte reals), a line with an odd factor 8 (or 9)
-// from 48 points on, where its outer stages then fill every lane; shorter ones
-// keep their odd factors in every thread, times up to 4 of the powers of two.
+// Elements per thread of a length-N line with at most 8: a line with an odd factor
+// 8 (or 9) from 48 points on, where its outer stages then fill every lane; shorter
+// ones keep their odd factors in every thread, times up to 4 of the powers of two.
+constexpr int elems8(int N) {
+    const int p2 = N / odd_part(N);
+    if (odd_part(N) == 1) return p2 < 8 ? p2 : 8;
+    if (mid_plan(N)) return N % 8 == 0 ? 8 : 9;
+    return odd_part(N) * (p2 < 4 ? p2 : 4);
+}
+// Elements per thread of a length-N line of the contiguous passes: a power of two
+// takes up to 16 in FP32.  Lines with a factor 3 or 5 keep it in every thread (12
+// or 20 elements) where that measured faster: in FP32 below 192 points (13
+// densities' P1 at n = 96 and 160 27 and 111 us, with 8 elements 31 and 124); in
+// FP64 with the factor 3 below 384 (13 densities' P1 and P5, 12 elements and 8, n = 48
+// 10.8 + 11.8 us and 12.1 + 14.2, n = 96 47 + 51 and 52 + 53, 32 of n = 192 SPLIT 850 +
+// 840 and 864 + 847; one of n = 384 253 + 259 and 237 + 235; n = 160 25.6 + 23.9 with 8
+// and 28.8 + 25.1 with 20).
 constexpr int elems_per_thread(int N, int real_bytes) {
-    int odd = N;
-    while (odd % 2 == 0) odd /= 2;
-    const int p2 = N / odd;
-    if (odd == 1) return p2 < (real_bytes == 8 ? 8 : 16) ? p2 : (real_bytes == 8 ? 8 : 16);
-    // (FP32 lines of 96 and 160 points: 13 densities' P1 27 and 111 us with 12
-    // and 20 elements, 31 and 124 us with 8)
-    if (mid_plan(N) && !(real_bytes == 4 && N < 192 && odd <= 5)) return N % 8 == 0 ? 8 : 9;
-    return odd * (p2 < 4 ? p2 : 4);
+    const int odd = odd_part(N);
+    if (odd == 1) return real_bytes == 8 ? elems8(N) : N < 16 ? N : 16;
+    if (mid_plan(N) && (real_bytes == 4 ? odd <= 5 && N < 192 : odd == 3 && N < 384)) return 4 * odd;
+    return elems8(N);
 }
 // Threads per line of the strided passes: at most 8 elements each; with an odd
 // factor the next power of two, so that 4 or 8 lines make workgroups of 4 or 8
@@ -369,7 +378,7 @@ constexpr int elems_per_thread(int N, int real_bytes) {
 // allow two, and the axis-1 forward pass took 0.86 ms.)  The idle threads of
 // the outer stages are whole waves and cost no issue slots.
 constexpr int strided_team(int N) {
-    const int t = N / elems_per_thread(N, 8);
+    const int t = N / elems8(N);
     if (!mid_plan(N) || N % 8 != 0) return t;
     int p = 1;
     while (p < t) p *= 2;

@@ -172,7 +172,7 @@ struct PlaneCfg {
     static constexpr int CX = sizeof(cx<Real>);
     // 8 elements per thread, or 12 with a factor 3 (two stages for 48 points and
     // not three: plane_conv 18.4 -> 12.6 us in FP64)
-    static constexpr int T = N / (odd_part(N) > 1 ? 4 * odd_part(N) : elems_per_thread(N, 8));
+    static constexpr int T = N / (odd_part(N) > 1 ? 4 * odd_part(N) : elems8(N));
     static constexpr int threads = N * T;
     static constexpr int pitch() {
         int p = LdsLine<Real>::slots(N);
@@ -474,7 +474,7 @@ template <int N, int DT, int NT, size_t LDS>
 struct Col0 {
     // a row pair has four teams, one for each row and parity of k0 (one team that
     // took both parities needed 30 registers more than P3 has in FP64)
-    static constexpr int T = 4 * Cfg<N, DT>::T3 <= NT ? Cfg<N, DT>::T3 : mid_plan(N) ? N / elems_per_thread(N, 8) : NT / 4;
+    static constexpr int T = 4 * Cfg<N, DT>::T3 <= NT ? Cfg<N, DT>::T3 : mid_plan(N) ? N / elems8(N) : NT / 4;
     // row pairs that the threads and that the LDS hold; threads past the last
     // pair only join the barriers, on one more region of LDS
     static constexpr int gt = NT / (4 * T), gl = int(LDS / (size_t(4) * N * Cfg<N, DT>::CX));
@@ -1226,7 +1226,7 @@ struct Sched {
     static constexpr int odd = odd_part(N);
     static constexpr bool mid = mid_plan(N);
     static constexpr int e16 = odd > 1 ? odd * 2 : elems_per_thread(N, 4), eo = odd * 4;
-    static constexpr int tm = N / elems_per_thread(N, 8);
+    static constexpr int tm = N / elems8(N);
     static constexpr TileV pick24(TileV v) { return tile_ok(N, v, C::CX, C::IP, false) ? v : d24; }
     static constexpr TileV pick3(TileV v) { return tile_ok(N, v, C::CX, C::IP, true) && C::BS % v.B == 0 ? v : d3; }
     static constexpr TileV v24[psn_host::kScheduleCandidates] = {
@@ -1273,8 +1273,8 @@ struct SchedP {
     static constexpr TileP d3{C::BP3, T, 1, 2};
     static constexpr TileP v3[psn_host::kScheduleCandidates] = {
         d3, pick_tilep(N, TileP{C::BP3, T, 2, 2}, d3, C::CX, C::BS),
-        pick_tilep(N, TileP{C::BP3, mid_plan(H) ? H / elems_per_thread(H, 8) : H / e4, 1, 2}, d3, C::CX, C::BS),
-        pick_tilep(N, mid_plan(H) ? TileP{C::BP3, H / elems_per_thread(H, 8), 2, 2} : TileP{C::BP3, H / e16, 1, 2}, d3,
+        pick_tilep(N, TileP{C::BP3, mid_plan(H) ? H / elems8(H) : H / e4, 1, 2}, d3, C::CX, C::BS),
+        pick_tilep(N, mid_plan(H) ? TileP{C::BP3, H / elems8(H), 2, 2} : TileP{C::BP3, H / e16, 1, 2}, d3,
                    C::CX, C::BS)};
 };
 
