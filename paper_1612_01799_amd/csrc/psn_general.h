@@ -60,17 +60,20 @@ struct GArgs {
 // walk along it; the skew of one slot per 16 and a pitch of 8 mod 32 spread a
 // wave's accesses over the banks); the strided steps keep the lines as columns
 // (consecutive lanes, consecutive lines), both chains side by side.  All need
-// the length-FL table exp(-2 pi i m / L), m < 2 FL.  The strided steps take at
-// most 8 elements per thread, so that enough waves fit beside their LDS.
+// the length-FL table exp(-2 pi i m / L), m < 2 FL.
 template <int L, class Real, int STEP>
 struct GCfg {
     static constexpr bool rows = STEP == 1 || STEP == 5;
     static constexpr int FL = L / 2;
-    // (the axis-0 step keeps 12 or 20 elements per thread at n0 = 384 and 320:
-    // 1.07 against 1.33 ms at 384 x 512 x 512 FP32 for 64 threads per line)
+    // The strided steps take at most 8 elements per thread, so that enough waves fit
+    // beside their LDS, but the axis-0 step keeps 12 at n0 = 96, 192 and 384 and 20 at
+    // n0 = 320: 1.07 against 1.33 ms at 384 x 512 x 512 FP32 for 64 threads per line;
+    // n0 x 512 x 384 with 12 elements and with strided_team, n0 = 96 FP32 209 and
+    // 224 us, FP64 345 and 362, n0 = 192 401 and 416, 703 and 729.  (n0 = 48 125 with
+    // 12, 99 without; n0 = 160 386 with 20, 388 without, FP64 845 and 633.)
+    static constexpr bool wide0 = mid_plan(FL) && (FL >= 256 || (odd_part(FL) == 3 && FL >= 96));
     static constexpr int T = rows ? FL / elems_per_thread(FL, int(sizeof(Real)))
-                             : STEP == 3 && FL >= 256 && mid_plan(FL) ? FL / (4 * odd_part(FL))
-                                                                      : strided_team(FL);
+                             : STEP == 3 && wide0 ? FL / (4 * odd_part(FL)) : strided_team(FL);
     static constexpr int E = FL / T;  // elements per thread (the row steps: exactly)
     static constexpr int CX = sizeof(cx<Real>);
     // The axis-0 step at n0 >= 512 reads its stage twiddles from per-stage
