@@ -70,9 +70,12 @@ def oracle_workers():
 def pass_bytes(n, dtype):
     """Algorithmic bytes of P1..P5: each array read and written once.  b1, b2:
     bytes of one complex element of W1 (n^3) and W2 (2 n^3); split precision
-    keeps W1 in 12-byte elements and W2 in FP64."""
+    keeps W1 in 12-byte elements and W2 in FP64.  Cubes of n <= 64 run P2, P3 and
+    P4 as one pass (timed as P3) from W1 to W2, which P5 reads."""
     bio, b1, b2, bk = {"f32": (4, 8, 8, 4), "f64": (8, 16, 16, 8), "split": (8, 12, 16, 8)}[dtype]
     n3 = float(n) ** 3
+    if n <= 64:
+        return [(bio + b1) * n3, 0.0, (b1 + 2 * b2) * n3 + bk * (n + 1.0) ** 3, 0.0, (2 * b2 + bio) * n3]
     return [(bio + b1) * n3, (b1 + 2 * b2) * n3, 4 * b2 * n3 + bk * (n + 1.0) ** 3, (2 * b2 + b1) * n3,
             (b1 + bio) * n3]
 

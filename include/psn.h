@@ -91,7 +91,8 @@ typedef struct {
     double C0, C2;      /* correction constants; valid once built */
     int built;          /* 1 after psn_kernel_build succeeded */
     size_t device_bytes;     /* device memory held by the plan */
-    double algorithmic_bytes;/* HBM bytes one solve must move (five pruned passes) */
+    double algorithmic_bytes;/* HBM bytes one solve must move: its pruned passes (five; three for cubes of n <= 64),
+                              * each reading and writing its arrays once */
     double a[3], b[3];  /* the box [a0,b0] x [a1,b1] x [a2,b2] */
     double h3[3];       /* grid spacing per axis */
     double T3[3];       /* kernel truncation per axis */

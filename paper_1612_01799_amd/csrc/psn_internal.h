@@ -53,12 +53,16 @@ constexpr int kMaxBatchHost = 32;
 
 namespace psn_host {
 
+// Largest cube whose axes 1 and 0 run plane by plane in one launch (plane_conv;
+// PlaneCfg in psn_passes.h has the figures).
+constexpr int kPlaneMax = 64;
+
 // Kernel spectrum layout: planes of (n+1) x n reals per folded k~1, each tiled
 // over k2 as [k2 / KT][k~0][k2 % KT] with KT the largest of 8, 4, 2, 1 dividing
 // n, so the middle pass's workgroup (one k~1, a tile of k2) reads one run; KT = 1
-// up to n = 64, where a workgroup has one k2 (plane_conv).
+// up to n = kPlaneMax, where a workgroup has one k2 (plane_conv).
 __host__ __device__ constexpr int k_tile(int n) {
-    return n <= 64 ? 1 : n % 8 == 0 ? 8 : n % 4 == 0 ? 4 : n % 2 == 0 ? 2 : 1;
+    return n <= kPlaneMax ? 1 : n % 8 == 0 ? 8 : n % 4 == 0 ? 4 : n % 2 == 0 ? 2 : 1;
 }
 __host__ __device__ constexpr size_t k_index(int n, int kt1, int kt0, int k2) {
     return (size_t(kt1) * (n / k_tile(n)) + k2 / k_tile(n)) * size_t(n + 1) * k_tile(n) + size_t(kt0) * k_tile(n) +

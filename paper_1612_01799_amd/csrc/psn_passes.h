@@ -180,7 +180,7 @@ struct PlaneCfg {
         return p;
     }
     static constexpr size_t lds = size_t(N * pitch() + TwLds<Real>::slots(N)) * CX;
-    static constexpr bool value = N <= 64;
+    static constexpr bool value = N <= psn_host::kPlaneMax;
     static_assert(!value || (threads <= 1024 && lds <= size_t(kMaxLdsP3)), "a plane fits a workgroup");
 };
 

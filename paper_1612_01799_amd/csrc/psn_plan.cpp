@@ -362,7 +362,7 @@ psn_status tune_schedule(psn_plan* p, hipStream_t s) {
 
 size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
-// HBM bytes one solve must move: five passes, each one read and one write of
+// HBM bytes one solve must move: its passes, each one read and one write of
 // its arrays (io: rho and u, s: complex intermediates per real, k: kernel
 // spectrum per real)
 double algorithmic_bytes(const psn_plan* p) {
@@ -376,10 +376,13 @@ double algorithmic_bytes(const psn_plan* p) {
         return 2 * bio * n0 * n1 * n2 + 24 * bs * n0 * n1 * (n2 + 1) + bk * (n0 + 1) * (n1 + 1) * (n2 + 1);
     }
     // W1 (n^3 complex) is written and read twice (P1, P2, P4, P5), W2 (2 n^3
-    // complex) four times (P2, P3 read and write, P4)
+    // complex) four times (P2, P3 read and write, P4); the small cubes' three
+    // passes write and read each of them once
     const double n3 = double(p->n) * p->n * p->n, np1 = p->n + 1.0;
     const double b1 = double(psn_host::w1_bytes(p->dtype)), b2 = double(psn_host::w2_bytes(p->dtype));
-    return 2 * bio * n3 + 4 * b1 * n3 + 8 * b2 * n3 + bk * np1 * np1 * np1;
+    const double kernel = bk * np1 * np1 * np1;
+    if (p->n <= psn_host::kPlaneMax) return 2 * bio * n3 + 2 * b1 * n3 + 4 * b2 * n3 + kernel;
+    return 2 * bio * n3 + 4 * b1 * n3 + 8 * b2 * n3 + kernel;
 }
 
 // complex workspace elements of a grid with per-axis sizes (rows padded to
