@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <mutex>
 #include <new>
@@ -99,8 +100,14 @@ double gs_max_rel_error(const std::vector<double>& tau, const std::vector<double
     const int nt = int(std::max(1u, std::min(8u, std::thread::hardware_concurrency())));
     auto parallel = [&](auto&& part) {
         std::vector<std::thread> pool;
-        for (int k = 1; k < nt; ++k) pool.emplace_back([&part, k] { part(k); });
+        int made = 1;
+        try {
+            pool.reserve(nt);
+            for (; made < nt; ++made) pool.emplace_back([&part, made] { part(made); });
+        } catch (const std::exception&) {  // no thread or no memory: the parts left are taken here
+        }
         part(0);
+        for (; made < nt; ++made) part(made);
         for (auto& th : pool) th.join();
     };
     const double want = std::fabs(b - a) / 0.2;
