@@ -216,9 +216,7 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
             d2[0][e] = live ? gld(x + long(p) * hw) : cx<Real>{Real(0), Real(0)};
             d2[1][e] = d2[0][e] * a.tw[2 * p];
         });
-        // the exchange's addresses are not those of the input positions kept: at n1 = 256
-        // and 512 FP32 62 VGPRs instead of 66, so that a CU holds 8 waves per SIMD and not 7
-        Ff::template run<2>(d2, here(t), tl, lds);
+        Ff::template run<2>(d2, t, tl, lds);
         // output k1 = 2m + chain.  The workgroup's 2 n1 x B outputs are one
         // tile of W2 in each of the 2 n1 / KB k1 blocks, each a run of KB B
         // elements.  Stage them in LDS in k1-major order, then store the runs,
@@ -328,11 +326,8 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
         });
         Fi::template run<2>(d2, t, tl, lds);
         cx<Real>* y = a.w1 + i0 * n1 * hw + k2;
-        // the output positions are formed anew instead of being kept: at n1 = 256 and
-        // 512 FP32 62 VGPRs instead of 68, so that a CU holds 8 waves per SIMD and not 7
-        const int to = here(t);
-        Fi::each_out(to, [&](int e) {
-            const int p = Fi::out_pos(to, e);
+        Fi::each_out(t, [&](int e) {
+            const int p = Fi::out_pos(t, e);
             if (live) gst(y + long(p) * hw, twfma<+1>(d2[1][e], a.tw[2 * p], d2[0][e]));
         });
     } else {
