@@ -92,9 +92,13 @@ __host__ __device__ constexpr size_t g_k_index(int n0, int n2, int k0, int k1, i
 // costs the same in both modes (n = 512 FP32: 4.16 -> 2.99 ms, the five passes
 // over the density's half spectrum gone).  kCorrectionNone: the G-tensor alone.
 constexpr int kCorrectionNone = 2;  // beside the values of psn_correction
-__host__ __device__ constexpr double correction_weight(int mode, int k0, int k1, int k2) {
-    return mode == PSN_CORRECTION_FOLDED ? 1.0
-           : mode == PSN_CORRECTION_FOURIER && ((k0 | k1 | k2) & 1) == 0 ? 8.0 : 0.0;
+struct CorrectionWeight {
+    double even, other;  // where all three k are even, elsewhere
+    __host__ __device__ constexpr double at(int k0, int k1, int k2) const { return ((k0 | k1 | k2) & 1) ? other : even; }
+};
+constexpr CorrectionWeight correction_weight(int mode) {
+    return mode == PSN_CORRECTION_FOLDED ? CorrectionWeight{1.0, 1.0}
+           : mode == PSN_CORRECTION_FOURIER ? CorrectionWeight{8.0, 0.0} : CorrectionWeight{0.0, 0.0};
 }
 
 // k1 block of the W2 layout: the largest power of two <= sqrt(2n) dividing 2n

@@ -208,7 +208,7 @@ __global__ void k_correction(const double* __restrict__ tau, const double* __res
 // (n = 128 64 -> 30 us, n = 512 70 -> 43).
 __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__ A1, const double* __restrict__ A2,
                        const double* __restrict__ w, int terms, int n, double p0, double p1, double p2,
-                       const double* __restrict__ Cc, int mode, double* __restrict__ Kn) {
+                       const double* __restrict__ Cc, psn_host::CorrectionWeight cw, double* __restrict__ Kn) {
     const int k0 = blockIdx.x * blockDim.x + threadIdx.x, k1 = blockIdx.y;
     if (k0 > n) return;
     const int np1 = n + 1;
@@ -218,7 +218,7 @@ __global__ void k_edge(const double* __restrict__ A0, const double* __restrict__
         s = fma(A0[size_t(j) * np1 + k0] * A1[size_t(j) * np1 + k1], w[j] * A2[size_t(j) * np1 + n], s);
     const double b0 = 2.0 * kPi * k0 / p0, b1 = 2.0 * kPi * k1 / p1, b2 = 2.0 * kPi * n / p2;
     Kn[size_t(k1) * np1 + k0] =
-        s + psn_host::correction_weight(mode, k0, k1, n) * (Cc[0] - (Cc[1] / 6.0) * (b0 * b0 + b1 * b1 + b2 * b2));
+        s + cw.at(k0, k1, n) * (Cc[0] - (Cc[1] / 6.0) * (b0 * b0 + b1 * b1 + b2 * b2));
 }
 
 // Octant assembly, k2 = 0..n-1: a workgroup of 256 threads computes a tile of
@@ -236,7 +236,7 @@ template <class Kt, bool SYM>
 __global__ void __launch_bounds__(256, 3) k_gemm(const double* __restrict__ A0, const double* __restrict__ A1,
                                               const double* __restrict__ A2, const double* __restrict__ w, int terms,
                                               int n, double p0, double p1, double p2,
-                                              const double* __restrict__ Cc, int mode,
+                                              const double* __restrict__ Cc, psn_host::CorrectionWeight cw,
                                               const double* __restrict__ Kn, double scale, Kt* __restrict__ K,
                                               Kt* __restrict__ Kb) {
     __shared__ double sa[kChunk][kTile0], sb[kChunk][kTile2], s1[kChunk];
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(256, 3) k_gemm(const double* __restrict__ A0, 
             const int k2 = k2b + 16 * c + li;
             if (k2 >= n) continue;
             const double b2 = 2.0 * kPi * k2 / p2;
-            const double v = acc[i][c][e] + psn_host::correction_weight(mode, k0, k1, k2) *
+            const double v = acc[i][c][e] + cw.at(k0, k1, k2) *
                                                 (C0 - (C2 / 6.0) * (q01 + b2 * b2));
             if (k2 == 0) {
                 const double e = Kn[size_t(k1) * np1 + k0];
@@ -424,15 +424,16 @@ hipError_t launch_kernel_build(const psn_plan* p, int mode, void* K, void* Kb, c
                                p->period[0], p->period[1], p->period[2], d_c, scale, static_cast<double*>(K));
         return hipGetLastError();
     }
+    const CorrectionWeight cw = correction_weight(mode);
     hipLaunchKernelGGL(psn::k_edge, dim3((n + 1 + 127) / 128, n + 1), dim3(128), 0, s, A[0], A[1], A[2], d_w, terms,
-                       n, p->period[0], p->period[1], p->period[2], d_c, mode, d_kn);
+                       n, p->period[0], p->period[1], p->period[2], d_c, cw, d_kn);
     const double M = 2.0 * n;
     const double scale = 1.0 / (M * M * M);
     const bool sym = A[0] == A[1];
     const dim3 grid((n + psn::kTile2 - 1) / psn::kTile2, (n + 1 + psn::kTile0 - 1) / psn::kTile0, n + 1);
 #define PSN_GEMM(KT, SYMV)                                                                                         \
     hipLaunchKernelGGL((psn::k_gemm<KT, SYMV>), grid, dim3(256), 0, s, A[0], A[1], A[2], d_w, terms, n,            \
-                       p->period[0], p->period[1], p->period[2], d_c, mode, d_kn, scale,                 \
+                       p->period[0], p->period[1], p->period[2], d_c, cw, d_kn, scale,                 \
                        static_cast<KT*>(K), static_cast<KT*>(Kb))
     if (p->dtype == PSN_F32) {
         if (sym) PSN_GEMM(float, true);

@@ -257,31 +257,39 @@ void free_device(psn_plan* p) {
     p->built = false;
 }
 
+// Device scratch of build_spectrum.
+struct SpectrumScratch {
+    DevBuf tau, w, gl, A, c;
+    psn_status alloc(const psn_plan* p) {
+        const int terms = (int)p->tau.size(), nmax = std::max(p->ng[0], std::max(p->ng[1], p->ng[2]));
+        size_t tot = 0;
+        psn_status st = PSN_OK;
+        if ((st = dev_alloc(&tau.p, terms * 8, &tot)) || (st = dev_alloc(&w.p, terms * 8, &tot)) ||
+            (st = dev_alloc(&gl.p, 32 * 8, &tot)) ||
+            (st = dev_alloc(&A.p, psn_host::kbuild_scratch_doubles(nmax, terms) * 8, &tot)) ||
+            (st = dev_alloc(&c.p, 2 * 8, &tot)))
+            return st;
+        return PSN_OK;
+    }
+};
+
 // The kernel spectrum of p's geometry in its storage type, with the correction
 // entering by `mode`, into K and Kb, and C0, C2 into cc.  Synchronises s.
-psn_status build_spectrum(const psn_plan* p, int mode, void* K, void* Kb, double* cc, hipStream_t s) {
+psn_status build_spectrum(const psn_plan* p, int mode, void* K, void* Kb, double* cc, const SpectrumScratch& d,
+                          hipStream_t s) {
     double gl[32];
     gauss_legendre16(gl, gl + 16);
     const int terms = (int)p->tau.size();
-    const int nmax = std::max(p->ng[0], std::max(p->ng[1], p->ng[2]));
-    DevBuf d_tau, d_w, d_gl, d_A, d_c;
-    size_t tot = 0;
-    psn_status st = PSN_OK;
-    if ((st = dev_alloc(&d_tau.p, terms * 8, &tot)) || (st = dev_alloc(&d_w.p, terms * 8, &tot)) ||
-        (st = dev_alloc(&d_gl.p, sizeof gl, &tot)) ||
-        (st = dev_alloc(&d_A.p, psn_host::kbuild_scratch_doubles(nmax, terms) * 8, &tot)) ||
-        (st = dev_alloc(&d_c.p, 2 * 8, &tot)))
-        return st;
-    double* const dgl = static_cast<double*>(d_gl.p);
-    bool ok = hip_ok(hipMemcpyAsync(d_tau.p, p->tau.data(), terms * 8, hipMemcpyHostToDevice, s), "copy tau") &&
-              hip_ok(hipMemcpyAsync(d_w.p, p->w.data(), terms * 8, hipMemcpyHostToDevice, s), "copy w") &&
-              hip_ok(hipMemcpyAsync(d_gl.p, gl, sizeof gl, hipMemcpyHostToDevice, s), "copy nodes");
-    ok = ok && hip_ok(psn_host::launch_kernel_build(p, mode, K, Kb, static_cast<double*>(d_tau.p),
-                                                    static_cast<double*>(d_w.p), terms, dgl, dgl + 16,
-                                                    static_cast<double*>(d_A.p), static_cast<double*>(d_c.p), s),
+    double* const dgl = static_cast<double*>(d.gl.p);
+    bool ok = hip_ok(hipMemcpyAsync(d.tau.p, p->tau.data(), terms * 8, hipMemcpyHostToDevice, s), "copy tau") &&
+              hip_ok(hipMemcpyAsync(d.w.p, p->w.data(), terms * 8, hipMemcpyHostToDevice, s), "copy w") &&
+              hip_ok(hipMemcpyAsync(d.gl.p, gl, sizeof gl, hipMemcpyHostToDevice, s), "copy nodes");
+    ok = ok && hip_ok(psn_host::launch_kernel_build(p, mode, K, Kb, static_cast<double*>(d.tau.p),
+                                                    static_cast<double*>(d.w.p), terms, dgl, dgl + 16,
+                                                    static_cast<double*>(d.A.p), static_cast<double*>(d.c.p), s),
                       "kernel-spectrum launch");
-    ok = ok && hip_ok(hipMemcpyAsync(cc, d_c.p, 2 * sizeof(double), hipMemcpyDeviceToHost, s), "copy C0/C2");
-    ok = hip_ok(hipStreamSynchronize(s), "hipStreamSynchronize") && ok;  // also before gl and the buffers go
+    ok = ok && hip_ok(hipMemcpyAsync(cc, d.c.p, 2 * sizeof(double), hipMemcpyDeviceToHost, s), "copy C0/C2");
+    ok = hip_ok(hipStreamSynchronize(s), "hipStreamSynchronize") && ok;  // also before gl and the scratch go
     return ok ? PSN_OK : PSN_EDEVICE;
 }
 
@@ -649,12 +657,14 @@ psn_status psn_kernel_build(psn_plan* p, void* stream) {
         twsrc = twf.data();
     }
     double cc[2] = {0, 0};
-    if (!hip_ok(hipMemcpyAsync(p->tw, twsrc, tw_entries * cxb, hipMemcpyHostToDevice, s), "copy twiddles"))
-        st = PSN_EDEVICE;
-    else
-        st = build_spectrum(p, p->correction, p->K, p->Kb, cc, s);
+    SpectrumScratch scr;  // all allocations before the first copy
+    if (!(st = scr.alloc(p))) {
+        if (!hip_ok(hipMemcpyAsync(p->tw, twsrc, tw_entries * cxb, hipMemcpyHostToDevice, s), "copy twiddles"))
+            st = PSN_EDEVICE;
+        else
+            st = build_spectrum(p, p->correction, p->K, p->Kb, cc, scr, s);
+    }
     if (st) {
-        (void)hipStreamSynchronize(s);  // the twiddle copy has left its host buffer
         free_device(p);
         return st;
     }
@@ -1046,8 +1056,10 @@ psn_status psn_kernel_download(const psn_plan* p, double* octant) {
         if (!hip_ok(hipGetDevice(&dev), "hipGetDevice") || !hip_ok(hipSetDevice(p->device), "hipSetDevice"))
             return PSN_EDEVICE;
         psn_status st = PSN_OK;
-        if (!(st = dev_alloc(&gk.p, hk.size(), &tot)) && !(st = dev_alloc(&gb.p, hb.size(), &tot)))
-            st = build_spectrum(p, psn_host::kCorrectionNone, gk.p, gb.p, cc, nullptr);
+        SpectrumScratch scr;
+        if (!(st = dev_alloc(&gk.p, hk.size(), &tot)) && !(st = dev_alloc(&gb.p, hb.size(), &tot)) &&
+            !(st = scr.alloc(p)))
+            st = build_spectrum(p, psn_host::kCorrectionNone, gk.p, gb.p, cc, scr, nullptr);
         if (!hip_ok(hipSetDevice(dev), "hipSetDevice") && !st) st = PSN_EDEVICE;
         if (st) return st;
         K = gk.p;
