@@ -138,8 +138,9 @@ psn_status psn_plan_create_grid(const int *n, const double *a, const double *b, 
  * of section 3): FP64 mode integrals, correction constants C0 and C2 and the
  * octant assembly, then conversion to the plan's storage type; also allocates
  * the solve workspace.  Then picks the tile schedule of the strided passes:
- * each has four compiled candidates, timed once per (n, precision) in the
- * process on this plan's workspace (set PSN_TUNE=0 to keep the defaults).
+ * each has four candidates (some sizes have fewer tiles; candidate 0 then stands
+ * in for the others), timed once per (n, precision) in the process on this
+ * plan's workspace (set PSN_TUNE=0 to keep the defaults).
  * With PSN_TUNE_CACHE naming a file, a schedule recorded there for the same
  * (n, precision) is taken without timing, and a newly timed one is appended,
  * so that separate processes pick the same candidates (candidates agree only

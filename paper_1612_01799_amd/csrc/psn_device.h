@@ -294,13 +294,12 @@ struct RadixPlan {
 };
 
 // Stages for a length-N transform with E elements per thread: odd radices
-// first (9 for two factors 3), each merged with a factor 4 or 2 into one prime-factor radix (20, 12,
+// first, each merged with a factor 4 or 2 into one prime-factor radix (20, 12,
 // 10, 6) where that divides both what is left of N and E; then the largest
 // power-of-two radix (<= 16) dividing both what is left of N and the
 // power-of-two part of E, so each stage gives every thread a whole number of
 // butterflies.
 constexpr int odd_radix(int f, int rem, int E) {
-    if (f == 3 && rem % 9 == 0 && E % 9 == 0) return 9;
     for (int p = 4; p >= 1; p /= 2)
         if (rem % (f * p) == 0 && E % (f * p) == 0) return f * p;
     return -1;
@@ -330,21 +329,20 @@ constexpr RadixPlan make_plan(int N, int E) {
 }
 
 // Lines of 48 points and more with an odd factor: three stages 8, m, g (9, 2, 9
-// for 162; 9, 9 for 81) with m the odd factor (6 for 384).  A thread then holds at most 8 to
+// for 162) with m the odd factor (6 for 384).  A thread then holds at most 8 to
 // 12 elements instead of the 12 to 20 that keeping the odd factor in every stage
 // takes; the N / R butterflies of a stage are dealt to the team in rounds, and
 // a partly filled round leaves threads idle (TeamFFT::has).
 constexpr bool mid_plan(int N) { return N >= 48 && (N & (N - 1)) != 0; }
+constexpr int odd_part(int N) { return N % 2 ? N : odd_part(N / 2); }
 // A team that holds 12 or 20 elements per thread still takes the stages that
 // keep the odd factor in every thread (384 = 12.4.4.2 on 32 threads).
-constexpr int odd_part(int N) { return N % 2 ? N : odd_part(N / 2); }
 constexpr RadixPlan team_plan(int N, int E) {
     if (!mid_plan(N) || (odd_part(N) <= 5 && E % (4 * odd_part(N)) == 0)) return make_plan(N, E);
     const int first = N % 8 == 0 ? 8 : 9, rem = N / first;
     int last = first;
     while (rem % last != 0) last = first == 8 ? last / 2 : last / 3;
     const int mid = rem / last;
-    if (mid == 1) return RadixPlan{2, {first, last}};
     return mid == 2 || mid == 3 || mid == 5 || mid == 6 ? RadixPlan{3, {first, mid, last}} : RadixPlan{-1, {}};
 }
 
@@ -371,12 +369,14 @@ constexpr int elems_per_thread(int N, int real_bytes) {
     if (mid_plan(N) && (real_bytes == 4 ? odd <= 5 && N < 192 : odd == 3 && N < 384)) return 4 * odd;
     return elems8(N);
 }
-// Threads per line of the strided passes: at most 8 elements each; with an odd
-// factor the next power of two, so that 4 or 8 lines make workgroups of 4 or 8
-// whole waves.  (Measured at n = 384 FP64: with 48 threads per line, 6 waves per
-// workgroup, only one workgroup was resident per CU where registers and LDS
-// allow two, and the axis-1 forward pass took 0.86 ms.)  The idle threads of
-// the outer stages are whole waves and cost no issue slots.
+// Threads per line of the strided passes: at most 8 elements each (9 at 162, whose
+// middle stage fills 10 slots); with an odd factor the next power of two, so that 4
+// or 8 lines make workgroups of whole waves.  (Measured at n = 384 FP64: with 48
+// threads per line, 6 waves per workgroup, only one workgroup was resident per
+// CU where registers and LDS allow two, and the axis-1 forward pass took 0.86
+// ms.)  In the outer stages the idle threads are the last ones of every line, so
+// with 8 lines whole waves of them cost no issue slots (n = 192, 320 and 384); at
+// n = 96 and 160 the last busy wave is half full.
 constexpr int strided_team(int N) {
     const int t = N / elems8(N);
     if (!mid_plan(N) || N % 8 != 0) return t;
@@ -870,7 +870,6 @@ struct Prec<DT_SPLIT> {
     using Io = double;
     using Kt = double;
 };
-
 
 // Workspace of complex values between passes.
 template <int DT>

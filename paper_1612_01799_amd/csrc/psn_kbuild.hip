@@ -4,7 +4,7 @@
 //   a_j(k)   = 2 int_0^T exp(-tau_j^2 y^2) cos(kappa_k y) dy,  kappa_k = 2 pi k / (2 n h)
 //   C0, C2   = int_{B_delta} (U - U_GS) dy,  int_{B_delta} |y|^2 (U - U_GS) dy
 //   K(k)     = sum_j w_j a_j(k0) a_j(k1) a_j(k2) + c(k) (C0 - (C2/6) |kappa|^2)
-// with c = correction_weight: 1, or 8 on the all-even frequencies alone.
+// with c = correction_weight: 1, 8 on the all-even frequencies alone, or 0.
 //
 // Mode integrals, by the size of tau T:
 // * tau T >= 6.1: the Gaussian's Fourier transform (the tail beyond T is
@@ -433,7 +433,7 @@ hipError_t launch_kernel_build(const psn_plan* p, int mode, void* K, void* Kb, c
     const dim3 grid((n + psn::kTile2 - 1) / psn::kTile2, (n + 1 + psn::kTile0 - 1) / psn::kTile0, n + 1);
 #define PSN_GEMM(KT, SYMV)                                                                                         \
     hipLaunchKernelGGL((psn::k_gemm<KT, SYMV>), grid, dim3(256), 0, s, A[0], A[1], A[2], d_w, terms, n,            \
-                       p->period[0], p->period[1], p->period[2], d_c, cw, d_kn, scale,                 \
+                       p->period[0], p->period[1], p->period[2], d_c, cw, d_kn, scale,                             \
                        static_cast<KT*>(K), static_cast<KT*>(Kb))
     if (p->dtype == PSN_F32) {
         if (sym) PSN_GEMM(float, true);

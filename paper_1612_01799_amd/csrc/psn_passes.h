@@ -37,14 +37,7 @@
 
 namespace psn {
 
-constexpr int kMaxLds = 65536;       // per workgroup for the one-chain passes
-constexpr int kMaxLdsP3 = 163840;    // gfx950: 160 KB of LDS per workgroup
-
-constexpr int pick_cols(int N, int bmax, int sets, int cxbytes, int T) {
-    for (int b = bmax; b >= 1; --b)
-        if (N % b == 0 && sets * b * N * cxbytes <= kMaxLds && sets * b * T <= 1024) return b;
-    return 1;
-}
+constexpr int kMaxLdsP3 = 163840;  // gfx950: 160 KB of LDS per workgroup
 
 constexpr int pick_cols_p3(int N, int bmax, int cxbytes, int T) {
     for (int b = bmax; b >= 1; --b)
@@ -141,7 +134,8 @@ struct PairW2 {
 };
 // FP64 arithmetic, n >= 96 (LaneW2): neighbouring lanes take the two i0 of a
 // pair in every strided pass, on tiles of 4 columns (4 columns x 2 i0 x 16
-// bytes).  n = 512: P2 + P3 + P4 4.93 -> 4.80 ms, n = 256: 0.64 -> 0.60 ms.
+// bytes).  n = 512: P2 + P3 + P4 4.93 -> 4.80 ms, n = 256: 0.64 -> 0.60 ms; a solve of
+// n = 192 SPLIT 333 -> 319 us, of 32 in a batch 9.16 -> 9.25 ms (W1 in pieces of 48 bytes).
 template <int N, int DT>
 struct LaneW2 {
     static constexpr bool value = DT != DT_F32 && N >= 96;
@@ -160,12 +154,15 @@ struct W1Index {
     }
 };
 
-// Cubes whose axes 1 and 0 run plane by plane in one launch (plane_conv): three
-// launches a solve instead of five (and one for column 0), up to n = 64.  One FP32 density: n = 32
-// 26 -> 15.5 us, n = 48 29 -> 19.5, n = 64 34 -> 23; FP64 35 -> 21 at n = 48,
-// 39 -> 30 at n = 64; 13 densities a launch 95 -> 85 us (n = 64 FP32).  At n = 96
-// FP32 one density still gains (57 -> 52 us), but a CU holds one workgroup of a
-// plane only, and 13 take 384 us instead of 279.
+// Cubes whose axes 1 and 0 run plane by plane in one launch (plane_conv), up to
+// n = 64: three launches a solve instead of five.  Three against five launches, the same
+// box, us a solve for one density and a batch of 13 and of 32:
+//   n = 32  FP32 15.2 / 22.3                      FP64 15.1 / 19.3
+//   n = 48  FP32 18.5 / 21.8                      FP64 20.8 / 25.8, 71 / 83, 136 / 158
+//   n = 64  FP32 22.1 / 25.3,  80 / 85, 153 / 166   FP64 28.5 / 32.5, 134 / 139, 323 / 384
+//                                              SPLIT 28.2 / 32.5, 132 / 132, 315 / 354
+// At n = 96 FP32 a CU holds one workgroup of a plane only: one density 52 us against
+// 46 in five launches, 13 of them 384 against 269.
 template <int N, int DT>
 struct PlaneCfg {
     using Real = typename Prec<DT>::Real;
@@ -419,9 +416,9 @@ p2_fwd(const Batch<DT> bt) {
 // of barriers and one 16-byte access per element serve both.  Workgroup ids
 // are dealt to the XCDs round robin; each XCD gets a contiguous run of units,
 // so tiles sharing 128-byte lines and rows sharing a kernel row meet in the
-// same L2.  All global loads (data, the pre/post twiddles of the odd chain and
-// the kernel values) are issued before any arithmetic; the stage twiddles come
-// from a copy of the table in LDS.  Column 0 (the packed k2 = 0 / k2 = n pair)
+// same L2.  The data and the pre-twiddles of the odd chain are loaded before any
+// arithmetic, the kernel values after the forward transform (but for EARLY, below);
+// the stage twiddles come from a copy of the table in LDS.  Column 0 (the packed k2 = 0 / k2 = n pair)
 // is col0_conv's, on workgroups of the same launch.
 template <int N>
 struct P3Rows {
@@ -547,7 +544,9 @@ __device__ __forceinline__ void col0_conv(const Batch<DT>& bt, int blk, void* sm
 }
 
 // Minimum waves per SIMD asked of the compiler for P3 with em slots per chain
-// and thread (TeamFFT::EM): what fits without spills.
+// and thread (TeamFFT::EM): what fits without spills in every default tile.  (Two
+// FP64 candidates spill: 12 threads a line at n = 96, 44 bytes; P4 with 8 at n = 96
+// and 32 at n = 384, 20 and 28.)
 constexpr int p3_waves(int em, bool f32) {
     if (f32) return em <= 9 ? 6 : em <= 10 ? 5 : em <= 12 ? 4 : em <= 20 ? 3 : 1;
     return em <= 9 ? 4 : em <= 12 ? 3 : 1;
@@ -671,9 +670,9 @@ p3_conv(const Batch<DT> bt) {
     // But for EARLY, few values stay live across the transforms, so that more
     // waves fit: the kernel values are loaded after the forward one, the twiddles
     // w again at the end, and the addresses of the exchanges are formed anew for
-    // the inverse (here) instead of being kept.  n = 512 FP64: 166 -> 126 VGPRs,
-    // four waves per SIMD instead of three, 2.55 -> 2.39 ms; n = 320 FP64:
-    // 212 -> 146, three instead of two.
+    // the inverse (here) instead of being kept.  n = 512 FP64: 166 -> 124 VGPRs,
+    // four waves per SIMD instead of three, 2.55 -> 2.39 ms; n = 320 FP64, with the
+    // three-stage teams: 212 -> 112, four instead of two.
     Ff::template run<2>(d, t, Tw{stw}, lds);
     if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);
     if constexpr (!EARLY || DT == DT_F32) load_k();
@@ -1187,20 +1186,22 @@ inline bool allow_lds(const void* fn, size_t bytes) {
 
 // ------------------------------------------------------------------ schedules
 // Tile shapes of the strided passes: B adjacent columns per workgroup, TT
-// threads per line.  Each pass has four compiled candidates; the autotuner
-// times them once per (n, precision) and keeps the fastest.  A candidate that
-// does not fit (LDS, threads, radix plan) is replaced by candidate 0.
-//   P2/P4 (they keep the W2 layout tile, B = BS), n a power of two or below 48:
-//     the two chains exchanged together, twice the elements per thread (an odd
-//     factor: half), the chains one after the other, four elements; n >= 48
-//     with an odd factor, the chains always one after the other but for the
-//     third: 8 elements on a power-of-two team, on N / 8 threads, together, and
-//     all odd factors in every thread (12 or 20 elements).
+// threads per line.  Each pass has four candidates; the autotuner times them once
+// per (n, precision) and keeps the fastest.  A candidate that does not fit (LDS,
+// threads, radix plan) or is not there for a size is candidate 0 again: the axis-0
+// pass has three of its own at FP64 n = 128, 256 and 512, two at FP64 and one at FP32
+// n = 162, P2/P4 two at n = 162.
+//   P2/P4 (they keep the W2 layout tile, B = BS), n a power of two: the two chains
+//     together in FP32, one after the other in FP64 (LaneW2); twice the elements
+//     per thread; the other way of the two; four elements.  With an odd factor, the
+//     chains one after the other but for the third: 8 elements on a power-of-two
+//     team, on N / 8 threads, together, and all odd factors in every thread (12 or
+//     20 elements).
 //   P3: one row with the chains one after the other; the row pair k1, M-k1; the
-//     chains together (FP32 with an odd factor: 12 or 20 elements, the row pair,
-//     which is the fastest for many densities per launch: 13 of 160^3 0.51 against
-//     0.54 ms, while one density takes 67 against 51 us); with an odd factor, 8
-//     elements on N / 8 threads.
+//     chains together, or with an odd factor (in FP64 only 3) the row pair on 12
+//     or 20 elements, the fastest for many densities per launch (13 of 160^3 FP32
+//     0.51 against 0.54 ms, while one density takes 67 against 51 us; n = 96 and 192:
+//     p3_conv); with an odd factor, 8 elements on N / 8 threads.
 // The one-chain exchange stages the W2 runs of P2 in two rounds of n slots.
 struct TileV {
     int B, TT;
@@ -1216,23 +1217,21 @@ constexpr bool tile_ok(int N, TileV v, int cxbytes, int ip, bool axis0) {
     return v.B >= 1 && v.TT >= 1 && (v.SL == 1 || v.SL == 2) && N % v.B == 0 && v.TT <= N && (mid_plan(N) || N % v.TT == 0) &&
            lines * v.TT <= 1024 && ((v.SEQ ? 1 : 2) * lines * N + ((2 * N + 15) & ~15)) * cxbytes <= kMaxLdsP3 &&
            (!axis0 || v.TT % ip == 0) && team_plan(N, N / v.TT).n > 0 && N / v.TT <= 20;
-    
 }
 
 template <int N, int DT>
 struct Sched {
     using C = Cfg<N, DT>;
     static constexpr TileV d24{C::BS, C::T24, 1, mid_plan(N) || C::IP == 2}, d3{C::BP3, C::T3, N % 4 ? 2 : 1, true};  // 162: the row pair, whose 108 threads hold column 0's teams
-    static constexpr int odd = odd_part(N);
+    static constexpr int odd = odd_part(N), eo = 4 * odd;
     static constexpr bool mid = mid_plan(N);
-    static constexpr int e16 = odd > 1 ? odd * 2 : elems_per_thread(N, 4), eo = odd * 4;
     static constexpr int tm = N / elems8(N);
     static constexpr TileV pick24(TileV v) { return tile_ok(N, v, C::CX, C::IP, false) ? v : d24; }
     static constexpr TileV pick3(TileV v) { return tile_ok(N, v, C::CX, C::IP, true) && C::BS % v.B == 0 ? v : d3; }
     static constexpr TileV v24[psn_host::kScheduleCandidates] = {
-        d24, pick24(mid ? TileV{C::BS, tm, 1, true} : TileV{C::BS, N / e16}),
+        d24, pick24(mid ? TileV{C::BS, tm, 1, true} : TileV{C::BS, N / 16}),
         pick24(TileV{C::BS, C::T24, 1, !d24.SEQ}),
-        pick24(mid ? TileV{C::BS, N / eo, 1, true} : TileV{C::BS, N / (odd > 1 ? eo : 4)})};
+        pick24(mid ? TileV{C::BS, N / eo, 1, true} : TileV{C::BS, N / 4})};
     static constexpr TileV v3[psn_host::kScheduleCandidates] = {
         d3, pick3(TileV{C::BP3, C::T3, 2, true}), pick3(mid && (DT == DT_F32 || odd == 3) ? TileV{C::BP3, N / eo, 2, true, odd == 3} : TileV{C::BP3, C::T3, d3.SL}),
         mid && N % 4 == 0 ? pick3(TileV{C::BP3, tm, 1, true}) : d3};
@@ -1283,17 +1282,20 @@ struct SchedP {
 // build with another table would name another tile.  0: one form, no candidates.
 template <int N, int DT>
 constexpr uint32_t sched_tag() {
-    if (PlaneCfg<N, DT>::value) return 0;
-    uint32_t h = 2166136261u;
-    auto add = [&](int v) { h = (h ^ uint32_t(v)) * 16777619u; };
-    auto tile = [&](const TileV& v) { add(v.B), add(v.TT), add(v.SL), add(v.SEQ), add(v.EARLY); };
-    add(Cfg<N, DT>::IP);
-    for (const TileV& v : Sched<N, DT>::v24) tile(v);
-    if constexpr (PairW2<N, DT>::value)
-        for (const TileP& v : SchedP<N, DT>::v3) add(v.B), add(v.TT), add(v.SL), add(v.G);
-    else
-        for (const TileV& v : Sched<N, DT>::v3) tile(v);
-    return h ? h : 1;
+    if constexpr (PlaneCfg<N, DT>::value) {
+        return 0;
+    } else {
+        uint32_t h = 2166136261u;
+        auto add = [&](int v) { h = (h ^ uint32_t(v)) * 16777619u; };
+        auto tile = [&](const TileV& v) { add(v.B), add(v.TT), add(v.SL), add(v.SEQ), add(v.EARLY); };
+        add(Cfg<N, DT>::IP);
+        for (const TileV& v : Sched<N, DT>::v24) tile(v);
+        if constexpr (PairW2<N, DT>::value)
+            for (const TileP& v : SchedP<N, DT>::v3) add(v.B), add(v.TT), add(v.SL), add(v.G);
+        else
+            for (const TileV& v : Sched<N, DT>::v3) tile(v);
+        return h ? h : 1;
+    }
 }
 template <int DT>
 uint32_t sched_tag_of(int n) {
@@ -1462,8 +1464,10 @@ hipError_t solve_n(const Batch<DT>& bt, hipStream_t s, hipEvent_t* ev, int v24, 
     return hipGetLastError();
 }
 
-// Time the candidates of the strided passes on one problem's workspace
-// (contents are irrelevant to the timing) and return the fastest indices.
+// Time the candidates of the strided passes on one problem's workspace and return
+// the fastest indices.  Its contents are what earlier work left: the ranking comes
+// out as on a density, though the times may not (the axis-0 pass of 32 of n = 192
+// FP64 took 3.31 ms on stale values and 3.65 on white noise, at a lower clock).
 template <int N, int DT>
 hipError_t tune_n(const Batch<DT>& bt, hipStream_t s, int* best24, int* best3) {
     *best24 = *best3 = 0;
@@ -1557,8 +1561,8 @@ hipError_t solve_group(const psn_host::Slot* slots, int count, hipStream_t s, hi
 }
 
 // Time the candidates on a batch group's own entries (their workspaces in
-// the batch arena; contents are irrelevant to the timing): the first
-// kMaxBatch of them in one launch, as the batch runs them.
+// the batch arena, with stale contents): the first kMaxBatch of them in one
+// launch, as the batch runs them.
 template <int DT>
 hipError_t tune_slots(const psn_host::Slot* slots, int count, hipStream_t s, int* best24, int* best3) {
     Batch<DT> bt{};
