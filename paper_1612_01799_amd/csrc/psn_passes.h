@@ -134,8 +134,8 @@ struct PairW2 {
 };
 // FP64 arithmetic, n >= 96 (LaneW2): neighbouring lanes take the two i0 of a
 // pair in every strided pass, on tiles of 4 columns (4 columns x 2 i0 x 16
-// bytes).  n = 512: P2 + P3 + P4 4.93 -> 4.80 ms, n = 256: 0.64 -> 0.60 ms; a solve of
-// n = 192 SPLIT 333 -> 319 us, of 32 in a batch 9.16 -> 9.25 ms (W1 in pieces of 48 bytes).
+// bytes).  n = 512: P2 + P3 + P4 4.93 -> 4.80 ms, n = 256: 0.64 -> 0.60 ms.  SPLIT's W1
+// then moves in pieces of 48 bytes: P1 + P5 of 32 of n = 192 0.83 + 0.81 -> 0.85 + 0.85 ms.
 template <int N, int DT>
 struct LaneW2 {
     static constexpr bool value = DT != DT_F32 && N >= 96;
