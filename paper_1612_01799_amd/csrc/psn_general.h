@@ -44,6 +44,24 @@ struct GArgs {
     int kbs;  // log2 kb
 };
 
+// Lines of the axis-0 step (2 n1 hw) from which it holds all odd factors in every
+// thread (GCfg WIDE: 12 elements, 20 at n0 = 320) and not at most 8 elements on a
+// power-of-two team; -1: never.  At n0 = 320 and 384 always (384 x 512 x 512 FP32 1.07
+// against 1.33 ms).  At n0 = 96 and 192 in a launch of many workgroups, where the idle
+// lanes of the narrow team's outer stages count; in a smaller one its waves, twice
+// as many, do.  Narrow and wide, us, n0 = 96: FP32 19.2 / 19.6 at 35 000 lines, 25.2 / 25.2 at 52 000, 59.5 / 53.2
+// at 135 000, 223 / 207 at 401 000; FP64 60.7 / 63.2 at 77 000, 129 / 124 at 135 000, 349 / 339.
+// n0 = 192: FP32 21.1 / 21.8 at 18 000, 48.1 / 45.1 at 52 000, 402 / 389; FP64 101 / 102 at
+// 52 000, 136 / 132 at 68 000, 715 / 683.  Never at n0 = 48 (99 / 125 at 401 000), 160 (388 /
+// 386, FP64 633 / 845) and 162.
+template <class Real>
+constexpr long wide_lines(int n0) {
+    if (!mid_plan(n0)) return -1;
+    if (n0 >= 256) return 0;
+    if (n0 < 96 || odd_part(n0) != 3) return -1;
+    return sizeof(Real) == 4 ? 50000 : n0 < 192 ? 100000 : 60000;
+}
+
 // Every step runs transforms of length FL = L/2 = n_q.  The axis-2 steps
 // (1, 5) transform the real line as n2/2 packed pairs.  The strided steps split
 // the padded length-L transform of a line whose second half is zero into two
@@ -60,20 +78,17 @@ struct GArgs {
 // walk along it; the skew of one slot per 16 and a pitch of 8 mod 32 spread a
 // wave's accesses over the banks); the strided steps keep the lines as columns
 // (consecutive lanes, consecutive lines), both chains side by side.  All need
-// the length-FL table exp(-2 pi i m / L), m < 2 FL.
-template <int L, class Real, int STEP>
+// the length-FL table exp(-2 pi i m / L), m < 2 FL.  The strided steps take at
+// most 8 elements per thread, so that enough waves fit beside their LDS, but for
+// the axis-0 step of wide_lines.
+template <int L, class Real, int STEP, bool WIDE = false>
 struct GCfg {
     static constexpr bool rows = STEP == 1 || STEP == 5;
     static constexpr int FL = L / 2;
-    // The strided steps take at most 8 elements per thread, so that enough waves fit
-    // beside their LDS, but the axis-0 step keeps 12 at n0 = 96, 192 and 384 and 20 at
-    // n0 = 320: 1.07 against 1.33 ms at 384 x 512 x 512 FP32 for 64 threads per line;
-    // n0 x 512 x 384 with 12 elements and with strided_team, n0 = 96 FP32 209 and
-    // 224 us, FP64 345 and 362, n0 = 192 401 and 416, 703 and 729.  (n0 = 48 125 with
-    // 12, 99 without; n0 = 160 386 with 20, 388 without, FP64 845 and 633.)
-    static constexpr bool wide0 = mid_plan(FL) && (FL >= 256 || (odd_part(FL) == 3 && FL >= 96));
-    static constexpr int T = rows ? FL / elems_per_thread(FL, int(sizeof(Real)))
-                             : STEP == 3 && wide0 ? FL / (4 * odd_part(FL)) : strided_team(FL);
+    // (row steps in FP64: 12 elements at n2 = 48, 49 + 51 us at 512 x 384 x 48 against 55 + 54
+    // with 8; at n2 = 96 and 192 8 is level there and 3 to 6 % faster on small grids)
+    static constexpr int T = FL / (rows ? (sizeof(Real) == 8 && FL >= 96 ? elems8(FL) : elems_per_thread(FL, int(sizeof(Real))))
+                                   : WIDE ? 4 * odd_part(FL) : FL / strided_team(FL));
     static constexpr int E = FL / T;  // elements per thread (the row steps: exactly)
     static constexpr int CX = sizeof(cx<Real>);
     // The axis-0 step at n0 >= 512 reads its stage twiddles from per-stage
@@ -116,10 +131,11 @@ struct GCfg {
     static constexpr size_t lds = size_t(B * NP + TWS) * CX;
 };
 
-template <int L, class Real, class Io, int STEP>
-__global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>::T), (GCfg<L, Real, STEP>::min_waves))
+template <int L, class Real, class Io, int STEP, bool WIDE>
+__global__ void __launch_bounds__((GCfg<L, Real, STEP, WIDE>::B * GCfg<L, Real, STEP, WIDE>::T),
+                                  (GCfg<L, Real, STEP, WIDE>::min_waves))
     g_step(const GArgs<Real, Io> a) {
-    using C = GCfg<L, Real, STEP>;
+    using C = GCfg<L, Real, STEP, WIDE>;
     constexpr int B = C::B, T = C::T;
     constexpr bool rows = STEP == 1 || STEP == 5;
     constexpr int FL = C::FL;
@@ -365,18 +381,30 @@ __global__ void __launch_bounds__((GCfg<L, Real, STEP>::B * GCfg<L, Real, STEP>:
     }
 }
 
-template <int L, class Real, class Io, int STEP>
+template <int L, class Real, class Io, int STEP, bool WIDE>
 hipError_t launch_g_step(const GArgs<Real, Io>& a, long nlines, hipStream_t s) {
-    using C = GCfg<L, Real, STEP>;
+    using C = GCfg<L, Real, STEP, WIDE>;
     if constexpr (C::lds > 65536) {
-        static const hipError_t ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&g_step<L, Real, Io, STEP>),
+        static const hipError_t ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&g_step<L, Real, Io, STEP, WIDE>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, int(C::lds));
         if (ok != hipSuccess) return ok;
     }
     const long groups = (nlines + C::B - 1) / C::B;
-    hipLaunchKernelGGL((g_step<L, Real, Io, STEP>), dim3(unsigned(8 * ((groups + 7) / 8))), dim3(C::B * C::T), C::lds,
-                       s, a);
+    hipLaunchKernelGGL((g_step<L, Real, Io, STEP, WIDE>), dim3(unsigned(8 * ((groups + 7) / 8))), dim3(C::B * C::T),
+                       C::lds, s, a);
     return hipSuccess;
+}
+
+template <int L, class Real, class Io, int STEP>
+hipError_t launch_g_form(const GArgs<Real, Io>& a, long nlines, hipStream_t s) {
+    constexpr long wide = STEP == 3 ? wide_lines<Real>(L / 2) : -1;
+    if constexpr (wide == 0) {
+        return launch_g_step<L, Real, Io, STEP, true>(a, nlines, s);
+    } else {
+        if constexpr (wide > 0)
+            if (nlines >= wide) return launch_g_step<L, Real, Io, STEP, true>(a, nlines, s);
+        return launch_g_step<L, Real, Io, STEP, false>(a, nlines, s);
+    }
 }
 
 // dispatch on the padded length L = 2 n of a compiled size n
@@ -384,7 +412,7 @@ template <class Real, class Io, int STEP>
 hipError_t g_step_n(int n, const GArgs<Real, Io>& a, long nlines, hipStream_t s) {
     switch (n) {
 #define PSN_CASE(NN) \
-    case NN: return launch_g_step<2 * NN, Real, Io, STEP>(a, nlines, s);
+    case NN: return launch_g_form<2 * NN, Real, Io, STEP>(a, nlines, s);
         PSN_FOR_EACH_SIZE(PSN_CASE)
 #undef PSN_CASE
         default: return hipErrorInvalidValue;

@@ -59,7 +59,8 @@ template <int N, class Real>
 void grid() {
     team<N, GCfg<2 * N, Real, 1>::T, Real>("grid axis 2");
     team<N, GCfg<2 * N, Real, 2>::T, Real>("grid axis 1");
-    team<N, GCfg<2 * N, Real, 3>::T, Real>("grid axis 0");
+    if constexpr (wide_lines<Real>(N) != 0) team<N, GCfg<2 * N, Real, 3>::T, Real>("grid axis 0");
+    if constexpr (wide_lines<Real>(N) >= 0) team<N, GCfg<2 * N, Real, 3, true>::T, Real>("grid axis 0");
 }
 int main() {
 #define TEAMS(N) cube<N, DT_F64>(), cube<N, DT_F32>(), cube<N, DT_SPLIT>(), grid<N, float>(), grid<N, double>();

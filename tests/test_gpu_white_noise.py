@@ -66,7 +66,9 @@ def test_batch(n):
 
 
 @pytest.mark.parametrize("n3", [(96, 162, 48), (162, 48, 96), (48, 96, 162), (192, 32, 160), (160, 192, 24),
-                                (384, 24, 48), (48, 320, 96), (512, 16, 64), (64, 128, 192)])
+                                (384, 24, 48), (48, 320, 96), (512, 16, 64), (64, 128, 192),
+                                # either side of the lines from which the axis-0 step holds 12 elements per thread
+                                (96, 192, 128), (96, 256, 256), (192, 96, 192), (192, 192, 128), (192, 256, 128)])
 def test_grid(n3):
     torch = torch_cuda()
     rho, ref = _case(n3)
